@@ -151,9 +151,8 @@ int moe_slot_table_sync(moe_slot_table* t, void* stream);
 int moe_rmsnorm_f16(const float* xi, int T, int d, void* x_f16, void* stream);
 
 /* Workspace bytes needed by moe_route / moe_preroute / moe_expert_ffn_int4_lora
- * for T tokens. The caller allocates it and zero-fills it once. The library
- * leaves its internal counters at zero after every call. Calls that share one
- * workspace must be ordered on one stream. */
+ * for T tokens. The caller allocates it (no initial contents needed). Calls that
+ * share one workspace must be ordered on one stream. */
 size_t moe_workspace_bytes(const moe_layer_spec* spec, int T);
 
 /*

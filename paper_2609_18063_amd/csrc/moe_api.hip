@@ -28,7 +28,7 @@ bool pow2_dim(int v) {
 }
 
 struct WsLayout {
-  size_t counters, logits, gx, ux, h, ag, au, adpart;
+  size_t logits, gx, ux, h, ag, au, adpart;
   size_t g_perm, g_tiles, g_tok, g_ntiles, g_h, g_xp, g_ax, g_adp;  // grouped (batched) path
   int g_max_tiles;
   size_t total;
@@ -44,7 +44,6 @@ WsLayout ws_layout(const moe_layer_spec* s, int T) {
     off = round_up(off + bytes, kAlign);
     return o;
   };
-  w.counters = take((size_t)T * sizeof(uint32_t));
   w.logits = take((size_t)T * s->n_experts * sizeof(float));
   w.gx = take((size_t)T * n * s->d_expert * sizeof(float));
   w.ux = take((size_t)T * n * s->d_expert * sizeof(float));
@@ -276,13 +275,13 @@ static int route_common(const moe_layer_spec* s, const void* x, const void* W, i
   if (ws_bytes < L.total) return MOE_ENOMEM;
   float* logits = logits_opt ? logits_opt : at<float>(ws, L.logits);
   const bool sg = s->routing == MOE_ROUTING_SIGMOID_GROUP;
-  hipError_t e = moe::launch_route(static_cast<const __half*>(x), static_cast<const __half*>(W), T,
-                                   s->n_experts, s->d_model, s->top_k, logits, sg ? nullptr : idx, w,
-                                   at<uint32_t>(ws, L.counters), static_cast<hipStream_t>(stream));
-  if (e == hipSuccess && sg)
-    e = moe::launch_topk_sigmoid_group(logits, nullptr, T, s->n_experts, s->top_k, s->n_groups,
-                                       s->top_groups, s->route_scale, idx, w,
-                                       static_cast<hipStream_t>(stream));
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  hipError_t e = moe::launch_router_logits(static_cast<const __half*>(x), static_cast<const __half*>(W), T,
+                                           s->n_experts, s->d_model, logits, st);
+  if (e == hipSuccess)
+    e = sg ? moe::launch_topk_sigmoid_group(logits, nullptr, T, s->n_experts, s->top_k, s->n_groups,
+                                            s->top_groups, s->route_scale, idx, w, st)
+           : moe::launch_topk(logits, T, s->n_experts, s->top_k, idx, w, st);
   return from_hip(e);
 }
 

@@ -25,9 +25,10 @@ struct FfnArgs {
 };
 
 hipError_t launch_rmsnorm(const float* xi, int T, int d, __half* x, hipStream_t st);
-hipError_t launch_route(const __half* x, const __half* W, int T, int E, int d, int K,
-                        float* logits, int32_t* idx, float* w, uint32_t* counters,
-                        hipStream_t st);
+// Router logits [T][E] = x [T][d] W [E][d]^T, fp32 (d a multiple of 512).
+hipError_t launch_router_logits(const __half* x, const __half* W, int T, int E, int d, float* logits,
+                                hipStream_t st);
+// Softmax-top-k of [T][E] logits, E <= 1024, K <= 32.
 hipError_t launch_topk(const float* logits, int T, int E, int K, int32_t* idx, float* w,
                        hipStream_t st);
 // Sigmoid-group top-k (App. A), E <= 256; bias [E] or null.

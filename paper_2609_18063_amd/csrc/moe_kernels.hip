@@ -41,75 +41,158 @@ __global__ void __launch_bounds__(256) rmsnorm_f16_kernel(const float* __restric
     x[(size_t)t * d + j] = __half(static_cast<_Float16>((double)row[j] * r));
 }
 
-// Router / prerouter logits for one token per grid row, then (if idx is
-// given) softmax-top-k by the last workgroup of that token to finish (a
-// counter in the workspace, left at zero afterwards).
-template <int RPW>
-__global__ void __launch_bounds__(256) route_kernel(const __half* __restrict__ x,
-                                                    const __half* __restrict__ W, int E, int d,
-                                                    int K, float* __restrict__ logits,
-                                                    int32_t* __restrict__ idx,
-                                                    float* __restrict__ wout,
-                                                    uint32_t* __restrict__ counters) {
-  const int t = blockIdx.y;
-  const int nch = d >> 3;
-  // x is read by every wave from the cache, in the same loads as the rows (a
-  // copy into LDS first would put a barrier and one more memory round trip
-  // ahead of the row loads)
-  const U4* xrow = reinterpret_cast<const U4*>(x + (size_t)t * d);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row0 = (blockIdx.x * 4 + wave) * RPW;
-  float acc[RPW];
-#pragma unroll
-  for (int r = 0; r < RPW; ++r) acc[r] = 0.f;
-  for (int c = lane; c < nch; c += kWave) {
-    const U4 xv = xrow[c];
-    U4 wv[RPW];
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-      const int e = row0 + r;
-      wv[r] = (e < E) ? ld16(W + (size_t)e * d + (size_t)c * 8) : U4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) acc[r] = dot8_h(wv[r], xv, acc[r]);
-  }
-  float* lt = logits + (size_t)t * E;
-#pragma unroll
-  for (int r = 0; r < RPW; ++r) {
-    const float s = wave_sum(acc[r]);
-    if (lane == 0 && row0 + r < E) st_agent(lt + row0 + r, s);
-  }
-  __threadfence();
-  __syncthreads();
-  __shared__ int last;
-  __shared__ uint32_t tk_scratch[64];
-  if (threadIdx.x == 0) {
-    const uint32_t prev = atomicAdd(&counters[t], 1u);
-    last = (prev == gridDim.x - 1);
-  }
-  __syncthreads();
-  if (!last) return;
-  __threadfence();
-  if (wave == 0 && idx) wave_topk<true>(lt, E, K, idx + (size_t)t * K, wout + (size_t)t * K, tk_scratch);
-  if (threadIdx.x == 0)
-    __hip_atomic_store(&counters[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Router / prerouter logits of a few tokens: one row of W per wave, one token
+// per grid row, two waves per workgroup, so that the rows of one token spread
+// over the chip and each wave has its whole row in flight. Latency-bound: with
+// the selection, 5.0 us a call at T = 1, d 2048, E 256. (The selection by the
+// last workgroup to finish, behind a counter, took 21 us: its two agent-scope
+// fences write back the L2, in every workgroup.)
+constexpr int kRouteRows = 2;
+__global__ void __launch_bounds__(64 * kRouteRows) route_rows_kernel(const __half* __restrict__ x,
+                                                                     const __half* __restrict__ W, int E,
+                                                                     int d, float* __restrict__ logits) {
+  const int t = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int e = blockIdx.x * kRouteRows + wave;
+  if (e >= E) return;
+  const __half* xr = x + (size_t)t * d;
+  const __half* wr = W + (size_t)e * d;
+  float acc = 0.f;
+#pragma unroll 4
+  for (int c = lane; c < (d >> 3); c += kWave) acc = dot8_h(ld16(wr + (size_t)c * 8), ld16(xr + (size_t)c * 8), acc);
+  acc = wave_sum(acc);
+  if (lane == 0) logits[(size_t)t * E + e] = acc;
 }
 
-// The same selection and weights by one 512-thread workgroup per token
-// (E <= 256, K <= 32): two-stage ranking of the keys (moe_xchg.h), a few
-// barriers instead of one wave's 32 ballot rounds.
-__global__ void __launch_bounds__(512) topk_block_kernel(const float* __restrict__ logits, int E, int K,
-                                                         int32_t* __restrict__ idx,
-                                                         float* __restrict__ w) {
-  __shared__ float lg[256];
-  __shared__ uint64_t keys[256];
-  __shared__ int part[256];
-  __shared__ uint64_t cand[128];
-  __shared__ uint64_t sorted[32];
-  const int t = blockIdx.x;
-  if ((int)threadIdx.x < E) lg[threadIdx.x] = logits[(size_t)t * E + threadIdx.x];
+// The same for many tokens, a dense contraction on the matrix cores: a
+// workgroup forms 16 MB tokens x 16 NB experts, its eight waves one eighth of
+// d each (a short chain of v_mfma_f32_16x16x32_f16 per accumulator, whose
+// operands are loaded straight from global memory in 64-byte row pieces); the
+// eight partial sums are added in LDS as a tree. Every row is read by
+// E / (16 NB) or T / (16 MB) workgroups from the L2. Rows past T or E read
+// the last row and are not stored. Bound by the L2 reads of the operands at
+// large T (203 MB in 31 us with 2 x 2 blocks at T = 3100, d 2048, E 256; 103 MB
+// with 4 x 4 blocks, 20.5 us), by one round trip at small T. With the selection,
+// at d 2048 / E 256: 8.6 us at T = 64, 12.5 at 512, 25 at 3100 (one wave per row
+// and token: 9.3, 37 and 187 us). Two chains per wave keep the error against
+// float64 below the row kernel's (9.4e-8 against 1.1e-7 of the logits).
+typedef _Float16 mf_h8 __attribute__((ext_vector_type(8)));
+typedef float mf_f4 __attribute__((ext_vector_type(4)));
+constexpr int kRouteWaves = 8;
+template <int MB, int NB>
+__global__ void __launch_bounds__(64 * kRouteWaves) route_mfma_kernel(const __half* __restrict__ x,
+                                                                      const __half* __restrict__ W, int T,
+                                                                      int E, int d,
+                                                                      float* __restrict__ logits) {
+  __shared__ float red[kRouteWaves][MB * NB][4][kWave];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int col = lane & 15, kq = lane >> 4;
+  const int nb = (E + 16 * NB - 1) / (16 * NB);
+  const int e0 = (blockIdx.x % nb) * 16 * NB, t0 = (blockIdx.x / nb) * 16 * MB;
+  const int kw = d / kRouteWaves;                // a multiple of 64 (d >= 512)
+  const int k0 = wave * kw + kq * 8;
+  const __half *xr[MB], *wr[NB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) xr[m] = x + (size_t)min(t0 + 16 * m + col, T - 1) * d + k0;
+#pragma unroll
+  for (int n = 0; n < NB; ++n) wr[n] = W + (size_t)min(e0 + 16 * n + col, E - 1) * d + k0;
+  constexpr int NC = 2;                          // two chains: the k steps of even and odd index
+  mf_f4 acc[NC][MB][NB];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int n = 0; n < NB; ++n) acc[c][m][n] = mf_f4{0.f, 0.f, 0.f, 0.f};
+  constexpr int KS = MB * NB == 1 ? 8 : MB * NB <= 4 ? 4 : 2;  // k steps whose loads are in flight at once
+  for (int k = 0; k < kw; k += 32 * KS) {
+    mf_h8 a[KS][MB], b[KS][NB];
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      const bool in = k + 32 * u < kw;           // uniform
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+        b[u][n] = in ? *reinterpret_cast<const mf_h8*>(wr[n] + k + 32 * u) : mf_h8{};
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+        a[u][m] = in ? *reinterpret_cast<const mf_h8*>(xr[m] + k + 32 * u) : mf_h8{};
+    }
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+          acc[u % NC][m][n] =
+              __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][m], b[u][n], acc[u % NC][m][n], 0, 0, 0);
+  }
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        red[wave][m * NB + n][i][lane] = acc[0][m][n][i] + acc[1][m][n][i];
   __syncthreads();
-  eng::block_topk(lg, E, K, idx + (size_t)t * K, w + (size_t)t * K, keys, part, cand, sorted);
+  // lane (col, kq) of block (m, n) holds tokens 16 m + 4 kq + i, expert 16 n + col
+  for (int p = threadIdx.x; p < MB * NB * 256; p += 64 * kRouteWaves) {
+    const int blk = p >> 8, i = (p >> 6) & 3, l = p & 63;
+    float v[kRouteWaves];
+#pragma unroll
+    for (int q = 0; q < kRouteWaves; ++q) v[q] = red[q][blk][i][l];
+    const float s = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    const int t = t0 + 16 * (blk / NB) + 4 * (l >> 4) + i, e = e0 + 16 * (blk % NB) + (l & 15);
+    if (t < T && e < E) logits[(size_t)t * E + e] = s;
+  }
+}
+
+// Softmax-top-k, one wave per token. Lane l holds the V logits l V .. l V + V - 1
+// as order keys; each of K rounds takes the largest key left over the wave
+// (ties: the lowest lane, then its lowest position, which is the lowest id). A
+// round is a dozen lane moves, so K <= 32 rounds need no barrier and no LDS:
+// 2.5 - 3.3 us a call up to T = 777 and 4.6 us at T = 3100 (E 256, K 8); one
+// 512-thread workgroup per token took 8.8 us there. For E 1000, 6.7 us; a wave
+// finding the K-th key bit by bit took 17 us.
+template <int V>
+__global__ void __launch_bounds__(256) topk_wave_kernel(const float* __restrict__ logits, int T, int E, int K,
+                                                        int32_t* __restrict__ idx, float* __restrict__ w) {
+  const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (t >= T) return;
+  const float* l = logits + (size_t)t * E;
+  uint32_t key[V];                               // 0: no logit, or taken (no real key is 0)
+#pragma unroll
+  for (int j = 0; j < V; ++j) key[j] = lane * V + j < E ? topk_key(l[lane * V + j]) : 0u;
+  uint32_t best = key[0];
+#pragma unroll
+  for (int j = 1; j < V; ++j) best = max(best, key[j]);
+  uint32_t mk = 0;                               // lane k: the k-th largest key and its id
+  int mi = 0;
+  for (int k = 0; k < K; ++k) {
+    const uint32_t m = wave_max_u32(best);
+    const int win = __builtin_ctzll(__ballot(best == m));
+    int pos = V - 1;
+#pragma unroll
+    for (int j = V - 2; j >= 0; --j) pos = key[j] == m ? j : pos;
+    const int id = __builtin_amdgcn_readlane(pos, win) + win * V;
+    if (lane == k) {
+      mk = m;
+      mi = id;
+    }
+    uint32_t nb = 0;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      key[j] = lane == win && j == pos ? 0u : key[j];
+      nb = max(nb, key[j]);
+    }
+    best = nb;
+  }
+  const float v = lane < K ? topk_key_value(mk) : 0.f;
+  const float mx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
+  const float ex = lane < K ? expf(v - mx) : 0.f;
+  const float sum = wave_sum(ex);
+  if (lane < K) {
+    idx[(size_t)t * K + lane] = mi;
+    w[(size_t)t * K + lane] = ex / sum;
+  }
 }
 
 // Sigmoid-group selection (App. A), one 512-thread workgroup per token
@@ -135,14 +218,6 @@ __global__ void __launch_bounds__(512) topk_sigmoid_group_kernel(const float* __
   __syncthreads();
   eng::block_topk_sigmoid_group(lg, bias, E, K, n_groups, top_groups, scale, idx + (size_t)t * K,
                                 w + (size_t)t * K, sc, keys, part, cand, sorted);
-}
-
-__global__ void __launch_bounds__(64) topk_kernel(const float* __restrict__ logits, int E, int K,
-                                                  int32_t* __restrict__ idx,
-                                                  float* __restrict__ w) {
-  __shared__ uint32_t tk_scratch[64];
-  const int t = blockIdx.x;
-  wave_topk<false>(logits + (size_t)t * E, E, K, idx + (size_t)t * K, w + (size_t)t * K, tk_scratch);
 }
 
 // ------------------------------------------------------------------------
@@ -490,19 +565,41 @@ __global__ void __launch_bounds__(256) chain_mix_rmsnorm_kernel(const __half* __
 // ------------------------------------------------------------------------
 // Launchers
 // ------------------------------------------------------------------------
+// Router logits: rows of W against one token at a time while that is little
+// work (T E d; it re-reads W for every token), else the matrix cores. Whole
+// calls, rows / 16 x 16 blocks: d 2048, E 256: 6.7 / 8.6 us at T = 24, 9.3 / 8.7
+// at 64; d 4096, E 64: 6.7 / 11.6 at 64, 21 / 11.8 at 512; d 512, E 16: 4.8 / 5.3
+// at 128, 6.1 / 5.4 at 512.
+constexpr int kRouteRowsMaxT = 128;
+constexpr long long kRouteRowsMaxWork = 1 << 24;
+// Larger blocks read less from the L2 but leave CUs idle when few: 2 x 2 blocks
+// of 16 from 160 workgroups on (16 x 16 / 32 x 32: 12.4 / 12.7 us with 128, 19 /
+// 12.9 with 200), 4 x 4 from 150 on (32 x 32 / 64 x 64: 21.3 / 22.4 us with 96,
+// 36 / 25 with 196).
+constexpr int kRouteFill22 = 160;
+constexpr int kRouteFill44 = 150;
 hipError_t launch_rmsnorm(const float* xi, int T, int d, __half* x, hipStream_t st) {
   hipLaunchKernelGGL(rmsnorm_f16_kernel, dim3(T), dim3(256), 0, st, xi, d, x);
   return hipGetLastError();
 }
 
-hipError_t launch_route(const __half* x, const __half* W, int T, int E, int d, int K,
-                        float* logits, int32_t* idx, float* w, uint32_t* counters,
-                        hipStream_t st) {
-  constexpr int RPW = 2;
-  const int rows_per_wg = 4 * RPW;
-  dim3 grid((E + rows_per_wg - 1) / rows_per_wg, T);
-  hipLaunchKernelGGL(route_kernel<RPW>, grid, dim3(256), 0, st, x, W, E, d, K, logits,
-                     idx, w, counters);
+hipError_t launch_router_logits(const __half* x, const __half* W, int T, int E, int d, float* logits,
+                                hipStream_t st) {
+  if (T <= kRouteRowsMaxT && (long long)T * E * d <= kRouteRowsMaxWork) {
+    hipLaunchKernelGGL(route_rows_kernel, dim3((E + kRouteRows - 1) / kRouteRows, T), dim3(64 * kRouteRows), 0, st,
+                       x, W, E, d, logits);
+    return hipGetLastError();
+  }
+  auto blocks = [&](int mb, int nb) { return ((T + 16 * mb - 1) / (16 * mb)) * ((E + 16 * nb - 1) / (16 * nb)); };
+  if (blocks(4, 4) >= kRouteFill44)
+    hipLaunchKernelGGL((route_mfma_kernel<4, 4>), dim3(blocks(4, 4)), dim3(64 * kRouteWaves), 0, st, x, W, T, E, d,
+                       logits);
+  else if (blocks(2, 2) >= kRouteFill22)
+    hipLaunchKernelGGL((route_mfma_kernel<2, 2>), dim3(blocks(2, 2)), dim3(64 * kRouteWaves), 0, st, x, W, T, E, d,
+                       logits);
+  else
+    hipLaunchKernelGGL((route_mfma_kernel<1, 1>), dim3(blocks(1, 1)), dim3(64 * kRouteWaves), 0, st, x, W, T, E, d,
+                       logits);
   return hipGetLastError();
 }
 
@@ -517,10 +614,11 @@ hipError_t launch_topk_sigmoid_group(const float* logits, const float* bias, int
 
 hipError_t launch_topk(const float* logits, int T, int E, int K, int32_t* idx, float* w,
                        hipStream_t st) {
-  if (E <= 256 && K <= 32)
-    hipLaunchKernelGGL(topk_block_kernel, dim3(T), dim3(512), 0, st, logits, E, K, idx, w);
+  const dim3 grid((T + 3) / 4), block(T == 1 ? 64 : 256);
+  if (E <= 256)
+    hipLaunchKernelGGL(topk_wave_kernel<4>, grid, block, 0, st, logits, T, E, K, idx, w);
   else
-    hipLaunchKernelGGL(topk_kernel, dim3(T), dim3(64), 0, st, logits, E, K, idx, w);
+    hipLaunchKernelGGL(topk_wave_kernel<16>, grid, block, 0, st, logits, T, E, K, idx, w);
   return hipGetLastError();
 }
 
