@@ -10,6 +10,8 @@
 // owns CPL = max(1, in/2048) chunks, so one wave instruction covers 64/LPR
 // rows with fully coalesced 16-byte loads.  A lane's chunks are the same for
 // every row it visits, so the 32*CPL activations it needs stay in registers.
+#include <algorithm>
+
 #include "moe_kernels.h"
 #include "moe_xchg.h"
 
@@ -19,26 +21,75 @@ namespace moe {
 // Layer input: RMS normalization to fp16.  The sum of squares, the scale and
 // the product are fp64 and the product is rounded once to fp16, so the fp16
 // rounding of every element does not depend on the order of the reduction.
+// A few tokens are latency-bound (one load, a wave reduction, one barrier, one
+// store); many are bound by memory. The row stays in registers between the sum
+// and the product: d 2048, T = 1 2.1 us, T = 3100 7.8 us (4.9 TB/s); 256 threads
+// with an eight-barrier tree, a second read of the row and the divide and
+// square root of 1 / sqrt took 4.6 and 16.6 us.
 // ------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) rmsnorm_f16_kernel(const float* __restrict__ xi, int d,
-                                                          __half* __restrict__ x) {
-  const int t = blockIdx.x;
-  const float* row = xi + (size_t)t * d;
+
+// 1 / sqrt(m) for m > 0, within a few fp64 ulps over the whole fp64 range (the
+// hardware estimate refined by two Newton steps); 0 for m = inf.
+__device__ __forceinline__ double rsqrt_full(double m) {
+  double y = __builtin_amdgcn_rsq(m);
+  y = y * (1.5 - 0.5 * (m * y) * y);
+  y = y * (1.5 - 0.5 * (m * y) * y);
+  return m == INFINITY ? 0.0 : y;
+}
+
+// Sum over the workgroup (whole waves), returned to every thread; red: one
+// double per wave.
+__device__ __forceinline__ double block_sum_f64(double v, double* red) {
+  v = eng::wave_sum_f64(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += red[i];
+  return s;
+}
+
+// d a multiple of 4, d <= 4 NV blockDim.x
+template <int NV>
+__global__ void __launch_bounds__(1024) rmsnorm_f16_kernel(const float* __restrict__ xi, int d,
+                                                           __half* __restrict__ x) {
+  __shared__ double red[16];
+  const float4* row = reinterpret_cast<const float4*>(xi + (size_t)blockIdx.x * d);
+  uint2* out = reinterpret_cast<uint2*>(x + (size_t)blockIdx.x * d);
+  const int nv = d >> 2;
+  float4 v[NV];
+  double acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int j = threadIdx.x + i * blockDim.x;
+    v[i] = j < nv ? row[j] : float4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const double a = v[i].x, b = v[i].y, c = v[i].z, e = v[i].w;
+    acc += (a * a + b * b) + (c * c + e * e);
+  }
+  const double r = rsqrt_full(block_sum_f64(acc, red) / (double)d + 1e-6);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int j = threadIdx.x + i * blockDim.x;
+    __half h[4] = {eng::f64_to_h((double)v[i].x * r), eng::f64_to_h((double)v[i].y * r),
+                   eng::f64_to_h((double)v[i].z * r), eng::f64_to_h((double)v[i].w * r)};
+    if (j < nv) out[j] = *reinterpret_cast<const uint2*>(h);
+  }
+}
+
+// Any d (rows that are not whole 16-byte pieces, or longer than the registers hold).
+__global__ void __launch_bounds__(256) rmsnorm_f16_any_kernel(const float* __restrict__ xi, int d,
+                                                              __half* __restrict__ x) {
+  __shared__ double red[4];
+  const float* row = xi + (size_t)blockIdx.x * d;
   double acc = 0.0;
   for (int j = threadIdx.x; j < d; j += blockDim.x) {
     const double v = row[j];
     acc += v * v;
   }
-  __shared__ double red[256];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double r = 1.0 / sqrt(red[0] / (double)d + 1e-6);
-  for (int j = threadIdx.x; j < d; j += blockDim.x)
-    x[(size_t)t * d + j] = __half(static_cast<_Float16>((double)row[j] * r));
+  const double r = rsqrt_full(block_sum_f64(acc, red) / (double)d + 1e-6);
+  for (int j = threadIdx.x; j < d; j += blockDim.x) x[(size_t)blockIdx.x * d + j] = eng::f64_to_h((double)row[j] * r);
 }
 
 // Router / prerouter logits of a few tokens: one row of W per wave, one token
@@ -518,48 +569,68 @@ __global__ void __launch_bounds__(256) combine_kernel(const float* __restrict__ 
 //   token start:  r = xi + rmsnorm(r)         (norm in fp64, r kept fp32)
 //   layer input:  r = r + D * r[perm];  x = fp16(rmsnorm(r))
 // ------------------------------------------------------------------------
-__device__ double block_sum_sq(const float* v, int d, double* red) {
+// Both are one workgroup of 1024 threads and latency-bound: each thread keeps
+// its d / 1024 elements in registers (NV of them) between the sum and the use
+// (the mixing at d 2048: 2.9 us; with 256 threads, re-reading r, 7.6 us).
+template <int NV>
+__global__ void __launch_bounds__(1024) chain_token_start_kernel(const float* __restrict__ xi, int d,
+                                                                 float* __restrict__ r) {
+  __shared__ double red[16];
+  float v[NV], xv[NV];
   double acc = 0.0;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    const double a = v[j];
-    acc += a * a;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int j = threadIdx.x + 1024 * i;
+    v[i] = j < d ? r[j] : 0.f;
+    xv[i] = j < d ? xi[j] : 0.f;
   }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = blockDim.x >> 1; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc += (double)v[i] * (double)v[i];
+  const double inv = rsqrt_full(block_sum_f64(acc, red) / (double)d + 1e-6);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int j = threadIdx.x + 1024 * i;
+    if (j < d) r[j] = (float)((double)xv[i] + (double)v[i] * inv);
   }
-  const double r = red[0];
-  __syncthreads();
-  return r;
 }
 
-__global__ void __launch_bounds__(256) chain_token_start_kernel(const float* __restrict__ xi, int d,
-                                                                float* __restrict__ r) {
-  __shared__ double red[256];
-  const double inv = 1.0 / sqrt(block_sum_sq(r, d, red) / (double)d + 1e-6);
-  for (int j = threadIdx.x; j < d; j += blockDim.x)
-    r[j] = (float)((double)xi[j] + (double)r[j] * inv);
-}
-
-__global__ void __launch_bounds__(256) chain_mix_rmsnorm_kernel(const __half* __restrict__ mix_d,
-                                                                const int32_t* __restrict__ perm,
-                                                                int d, float* __restrict__ r,
-                                                                __half* __restrict__ x) {
+template <int NV>
+__global__ void __launch_bounds__(1024) chain_mix_rmsnorm_kernel(const __half* __restrict__ mix_d,
+                                                                 const int32_t* __restrict__ perm, int d,
+                                                                 float* __restrict__ r,
+                                                                 __half* __restrict__ x) {
   extern __shared__ float rs[];
-  __shared__ double red[256];
-  for (int j = threadIdx.x; j < d; j += blockDim.x) rs[j] = r[j];
-  __syncthreads();
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    const int p = perm[j];
-    const float v = (p >= 0 && p < d) ? rs[p] : 0.f;
-    r[j] = fmaf(__half2float(mix_d[j]), v, rs[j]);
+  __shared__ double red[16];
+  float v[NV], m[NV];
+  int p[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int j = threadIdx.x + 1024 * i;
+    v[i] = j < d ? r[j] : 0.f;
+    p[i] = j < d ? perm[j] : -1;
+    m[i] = j < d ? __half2float(mix_d[j]) : 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int j = threadIdx.x + 1024 * i;
+    if (j < d) rs[j] = v[i];
   }
   __syncthreads();
-  const double inv = 1.0 / sqrt(block_sum_sq(r, d, red) / (double)d + 1e-6);
-  for (int j = threadIdx.x; j < d; j += blockDim.x)
-    x[j] = __half(static_cast<_Float16>((double)r[j] * inv));
+  double acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    v[i] = fmaf(m[i], (p[i] >= 0 && p[i] < d) ? rs[p[i]] : 0.f, v[i]);
+    acc += (double)v[i] * (double)v[i];
+  }
+  const double inv = rsqrt_full(block_sum_f64(acc, red) / (double)d + 1e-6);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int j = threadIdx.x + 1024 * i;
+    if (j < d) {
+      r[j] = v[i];
+      x[j] = eng::f64_to_h((double)v[i] * inv);
+    }
+  }
 }
 
 // ------------------------------------------------------------------------
@@ -578,8 +649,29 @@ constexpr long long kRouteRowsMaxWork = 1 << 24;
 // 36 / 25 with 196).
 constexpr int kRouteFill22 = 160;
 constexpr int kRouteFill44 = 150;
+template <int NV>
+static void rmsnorm(const float* xi, int T, int d, int threads, __half* x, hipStream_t st) {
+  hipLaunchKernelGGL(rmsnorm_f16_kernel<NV>, dim3(T), dim3(threads), 0, st, xi, d, x);
+}
+
 hipError_t launch_rmsnorm(const float* xi, int T, int d, __half* x, hipStream_t st) {
-  hipLaunchKernelGGL(rmsnorm_f16_kernel, dim3(T), dim3(256), 0, st, xi, d, x);
+  if (d % 4 || d > 8192) {
+    hipLaunchKernelGGL(rmsnorm_f16_any_kernel, dim3(T), dim3(256), 0, st, xi, d, x);
+    return hipGetLastError();
+  }
+  // one 16-byte piece per thread while the rows are few (latency: 2.1 us at T = 1,
+  // d 2048), four waves a row once they fill the chip several times over
+  const int most = T <= 512 ? 1024 : 256;
+  const int pieces = d / 4, threads = std::min(most, (pieces + 63) / 64 * 64);
+  const int nv = (pieces + threads - 1) / threads;
+  if (nv <= 1)
+    rmsnorm<1>(xi, T, d, threads, x, st);
+  else if (nv <= 2)
+    rmsnorm<2>(xi, T, d, threads, x, st);
+  else if (nv <= 4)
+    rmsnorm<4>(xi, T, d, threads, x, st);
+  else
+    rmsnorm<8>(xi, T, d, threads, x, st);
   return hipGetLastError();
 }
 
@@ -689,14 +781,24 @@ hipError_t launch_combine(const float* ye, const float* w, int T, int K, int S, 
 }
 
 hipError_t launch_chain_token_start(const float* xi, int d, float* r, hipStream_t st) {
-  hipLaunchKernelGGL(chain_token_start_kernel, dim3(1), dim3(256), 0, st, xi, d, r);
+  if (d <= 2048)
+    hipLaunchKernelGGL(chain_token_start_kernel<2>, dim3(1), dim3(1024), 0, st, xi, d, r);
+  else if (d <= 4096)
+    hipLaunchKernelGGL(chain_token_start_kernel<4>, dim3(1), dim3(1024), 0, st, xi, d, r);
+  else
+    hipLaunchKernelGGL(chain_token_start_kernel<8>, dim3(1), dim3(1024), 0, st, xi, d, r);
   return hipGetLastError();
 }
 
 hipError_t launch_chain_mix_rmsnorm(const __half* mix_d, const int32_t* perm, int d, float* r,
                                     __half* x, hipStream_t st) {
-  hipLaunchKernelGGL(chain_mix_rmsnorm_kernel, dim3(1), dim3(256), (size_t)d * 4, st, mix_d, perm, d,
-                     r, x);
+  const size_t lds = (size_t)d * 4;
+  if (d <= 2048)
+    hipLaunchKernelGGL(chain_mix_rmsnorm_kernel<2>, dim3(1), dim3(1024), lds, st, mix_d, perm, d, r, x);
+  else if (d <= 4096)
+    hipLaunchKernelGGL(chain_mix_rmsnorm_kernel<4>, dim3(1), dim3(1024), lds, st, mix_d, perm, d, r, x);
+  else
+    hipLaunchKernelGGL(chain_mix_rmsnorm_kernel<8>, dim3(1), dim3(1024), lds, st, mix_d, perm, d, r, x);
   return hipGetLastError();
 }
 
