@@ -547,6 +547,228 @@ __global__ void __launch_bounds__(256) ffn_down_kernel(FfnArgs a) {
 }
 
 // ------------------------------------------------------------------------
+// Stages 2 and 3 in one launch: every down workgroup forms its expert's whole h
+// (LoRA-B of gate / up, SwiGLU) and A_down h in LDS, then its output rows. The
+// operands that do not depend on h (gate / up sums, LoRA rows, the workgroup's
+// codes) are requested before the first barrier, so the three phases wait for
+// memory once. Both launches of a call, K + S 9, d 2048, I 512: 15.1 us at T = 1
+// and 104.6 at T = 24 (three launches: 26.3 and 141); K 4, d 4096, I 1024: 23.1 and
+// 170 us (32.4 and 227). Latency-bound at T = 1; passing the resolved bundle on
+// from the first launch changed nothing (15.1 and 15.5 us).
+// ------------------------------------------------------------------------
+
+// sum_k b[k] av[k] over the rank, k ascending; the first 16 of b preloaded.
+__device__ __forceinline__ float lora_b_dot(const U4& b0, const U4& b1, const __half* brow, const float* av,
+                                            int r) {
+  float acc = 0.f;
+  const uint32_t w[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float2 f = h2f2(w[i]);
+    if (2 * i < r) acc = fmaf(f.x, av[2 * i], acc);
+    if (2 * i + 1 < r) acc = fmaf(f.y, av[2 * i + 1], acc);
+  }
+  for (int k = 16; k < r; ++k) acc = fmaf(__half2float(brow[k]), av[k], acc);
+  return acc;
+}
+// elements k .. k + 7 of a row of r halves (zero past r)
+__device__ __forceinline__ U4 ld_rank8(const __half* row, int k, int r) {
+  U4 v{0, 0, 0, 0};
+  if (k >= r) return v;
+  if (r % 8 == 0) return ld16(row + k);
+  uint16_t e[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) e[i] = k + i < r ? reinterpret_cast<const uint16_t*>(row)[k + i] : (uint16_t)0;
+  v.x = e[0] | ((uint32_t)e[1] << 16);
+  v.y = e[2] | ((uint32_t)e[3] << 16);
+  v.z = e[4] | ((uint32_t)e[5] << 16);
+  v.w = e[6] | ((uint32_t)e[7] << 16);
+  return v;
+}
+
+// I = 32 LPR CPL <= 1024; a workgroup takes `batches` runs of 4 RIT 64 / LPR rows,
+// the codes of the next run in flight while one is summed.
+template <int LPR, int CPL, int RIT>
+__global__ void __launch_bounds__(256) ffn_hdown_kernel(FfnArgs a, int batches) {
+  constexpr int I = 32 * LPR * CPL;
+  constexpr int RPI = kWave / LPR;
+  constexpr int RUN = 4 * RIT * RPI;             // rows of one run
+  constexpr int IPT = (I + 255) / 256;           // h rows per thread
+  constexpr int PQ = I >= 512 ? I / 512 : 1;     // 8-element pieces of an A_down row per lane
+  constexpr int RW = 4;                          // A_down rows per wave requested ahead (rank <= 16)
+  constexpr int KMAX = 64 / LPR > 0 ? (64 + LPR - 1) / LPR : 1;
+  // h in 32-element pieces, 36 floats apart (the lanes of a row read one piece
+  // each: consecutive pieces on different banks)
+  __shared__ __align__(16) float hs[(I / 32) * 36];
+  __shared__ float av[2][64], ad[64];
+  const int t = blockIdx.y;
+  const int nblk = a.d / (RUN * batches);        // (powers of two)
+  const int k = blockIdx.x / nblk, b = blockIdx.x % nblk;
+  const int n = a.n_list, tid = threadIdx.x;
+  const size_t tk = (size_t)t * n + k;
+  float gv[IPT], uv[IPT];
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) {
+    const int i = tid + 256 * j;
+    gv[j] = i < I ? a.gx[tk * I + i] : 0.f;
+    uv[j] = i < I ? a.ux[tk * I + i] : 0.f;
+  }
+  const float avv = tid < 2 * a.r ? (tid < a.r ? a.ag[tk * a.r + tid] : a.au[tk * a.r + tid - a.r]) : 0.f;
+  const moe_bundle* bd = resolve_expert(k, a.K, a.E, a.idx + (size_t)t * a.K, a.slot_of,
+                                        a.bundles, a.status, false);
+  const int wave = tid >> 6, lane = tid & 63;
+  const int c0 = lane % LPR, sub = lane / LPR;
+  const int row0 = b * RUN * batches + wave * RIT * RPI + sub;  // this lane's first row
+  float* ye = a.y_experts + tk * a.d;
+  if (!bd) {
+    if (c0 == 0)
+      for (int rb = 0; rb < batches; ++rb)
+#pragma unroll
+        for (int it = 0; it < RIT; ++it) ye[row0 + rb * RUN + it * RPI] = 0.f;
+    return;
+  }
+  const bool has_g = a.r > 0 && bd->gate.lora_a && bd->gate.lora_b;
+  const bool has_u = a.r > 0 && bd->up.lora_a && bd->up.lora_b;
+  const bool has_lora = a.r > 0 && bd->down.lora_a && bd->down.lora_b;
+  const __half* bg = static_cast<const __half*>(bd->gate.lora_b);
+  const __half* bu = static_cast<const __half*>(bd->up.lora_b);
+  const __half* al = static_cast<const __half*>(bd->down.lora_a);
+  const __half* bl = static_cast<const __half*>(bd->down.lora_b);
+  const uint8_t* qd = static_cast<const uint8_t*>(bd->down.q);
+  const uint32_t* szd = static_cast<const uint32_t*>(bd->down.sz);
+
+  U4 gb[IPT][2], ub[IPT][2];
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) {
+    const int i = tid + 256 * j < I ? tid + 256 * j : 0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      gb[j][q] = has_g ? ld_rank8(bg + (size_t)i * a.r, 8 * q, a.r) : U4{0, 0, 0, 0};
+      ub[j][q] = has_u ? ld_rank8(bu + (size_t)i * a.r, 8 * q, a.r) : U4{0, 0, 0, 0};
+    }
+  }
+  U4 ar[RW][PQ];
+#pragma unroll
+  for (int m = 0; m < RW; ++m)
+#pragma unroll
+    for (int q = 0; q < PQ; ++q) {
+      const int c = lane + kWave * q;
+      ar[m][q] = has_lora && wave + 4 * m < a.r && c < I / 8 ? ld16(al + (size_t)(wave + 4 * m) * I + 8 * c)
+                                                             : U4{0, 0, 0, 0};
+    }
+  U4 wq[RIT][CPL];
+  uint32_t wsz[RIT][CPL];
+  uint16_t bv[RIT][KMAX];                        // LoRA-B of down: rank components c0, c0 + LPR, ...
+  auto load_run = [&](int rb) {
+#pragma unroll
+    for (int it = 0; it < RIT; ++it) {
+      const int j = row0 + rb * RUN + it * RPI;
+#pragma unroll
+      for (int cc = 0; cc < CPL; ++cc) {
+        const int c = c0 + LPR * cc;
+        wq[it][cc] = ld16(qd + (size_t)j * (I / 2) + (size_t)c * 16);
+        wsz[it][cc] = szd[(size_t)j * (I / 64) + (c >> 1)];
+      }
+#pragma unroll
+      for (int m = 0; m < KMAX; ++m) {
+        const int kk = c0 + LPR * m;
+        bv[it][m] = has_lora && kk < a.r ? reinterpret_cast<const uint16_t*>(bl)[(size_t)j * a.r + kk] : (uint16_t)0;
+      }
+    }
+  };
+  load_run(0);
+
+  if (tid < 2 * a.r) av[tid < a.r ? 0 : 1][tid < a.r ? tid : tid - a.r] = avv;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) {
+    const int i = tid + 256 * j;
+    if (i < I) {
+      float g = gv[j], u = uv[j];
+      if (has_g) g = fmaf(a.lora_scale, lora_b_dot(gb[j][0], gb[j][1], bg + (size_t)i * a.r, av[0], a.r), g);
+      if (has_u) u = fmaf(a.lora_scale, lora_b_dot(ub[j][0], ub[j][1], bu + (size_t)i * a.r, av[1], a.r), u);
+      hs[(i >> 5) * 36 + (i & 31)] = g / (1.f + expf(-g)) * u;
+    }
+  }
+  __syncthreads();
+  // A_down h, one rank row per wave and turn
+  if (has_lora) {
+    for (int m = 0; wave + 4 * m < a.r; ++m) {
+      const int kk = wave + 4 * m;
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < PQ; ++q) {
+        const int c = lane + kWave * q;
+        if (c < I / 8) {
+          U4 v = {0, 0, 0, 0};
+          if (m < RW) {
+#pragma unroll
+            for (int z = 0; z < RW; ++z)
+              if (m == z) v = ar[z][q];
+          } else {
+            v = ld16(al + (size_t)kk * I + 8 * c);
+          }
+          const float* hp = hs + (c >> 2) * 36 + (c & 3) * 8;
+          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float2 f = h2f2(w[i]);
+            s = fmaf(f.x, hp[2 * i], s);
+            s = fmaf(f.y, hp[2 * i + 1], s);
+          }
+        }
+      }
+      s = wave_sum(s);
+      if (lane == 0) ad[kk] = s;
+    }
+  }
+  float hf[CPL][32], hsum[CPL];
+#pragma unroll
+  for (int cc = 0; cc < CPL; ++cc) {
+    const float4* hp = reinterpret_cast<const float4*>(hs + (c0 + LPR * cc) * 36);
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float4 v = hp[q];
+      hf[cc][4 * q] = v.x;
+      hf[cc][4 * q + 1] = v.y;
+      hf[cc][4 * q + 2] = v.z;
+      hf[cc][4 * q + 3] = v.w;
+      s += (v.x + v.y) + (v.z + v.w);
+    }
+    hsum[cc] = s;
+  }
+  __syncthreads();
+  float adv[KMAX];
+#pragma unroll
+  for (int m = 0; m < KMAX; ++m) adv[m] = has_lora && c0 + LPR * m < a.r ? ad[c0 + LPR * m] : 0.f;
+  for (int rb = 0; rb < batches; ++rb) {
+    float acc[RIT];
+#pragma unroll
+    for (int it = 0; it < RIT; ++it) {
+      acc[it] = 0.f;
+#pragma unroll
+      for (int cc = 0; cc < CPL; ++cc) {
+        const float2 sz = h2f2(wsz[it][cc]);
+        acc[it] += sz.x * dot32_q4(wq[it][cc], hf[cc]) + sz.y * hsum[cc];
+      }
+      if (has_lora) {
+        float la = 0.f;
+#pragma unroll
+        for (int m = 0; m < KMAX; ++m) la = fmaf(__half2float(__ushort_as_half(bv[it][m])), adv[m], la);
+        acc[it] = fmaf(a.lora_scale, la, acc[it]);
+      }
+    }
+    if (rb + 1 < batches) load_run(rb + 1);
+#pragma unroll
+    for (int it = 0; it < RIT; ++it) {
+      const float s = group_sum(acc[it], LPR);
+      if (c0 == 0) ye[row0 + rb * RUN + it * RPI] = s;
+    }
+  }
+}
+
+// ------------------------------------------------------------------------
 // Combine: y = sum_k w_k y_k + sum_s y_shared_s.
 // ------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) combine_kernel(const float* __restrict__ ye,
@@ -736,6 +958,21 @@ static void down(const FfnArgs& a, int T, hipStream_t st) {
                      a);
 }
 
+// Rows per workgroup: enough runs that the launch still has 512 workgroups (two
+// a CU), so that the h of a workgroup is formed for as many rows as it can be.
+// Whole calls with 512 / 1024 / 2048: d 4096, I 1024, K 4: T = 4 45 / 52 / 64 us,
+// T = 24 170 / 175 / 186; d 2048, I 512, K + S 9: T = 8 45 / 46.5 / 51.
+constexpr int kHdownFill = 512;
+template <int LPR, int CPL>
+static void hdown(const FfnArgs& a, int T, hipStream_t st) {
+  constexpr int RIT = 4;
+  const int runs = a.d / (4 * RIT * (kWave / LPR));  // (d >= 512, a power of two: at least 4)
+  int batches = 1;
+  while (2 * batches <= runs && (long long)runs * a.n_list * T / (2 * batches) >= kHdownFill) batches *= 2;
+  hipLaunchKernelGGL((ffn_hdown_kernel<LPR, CPL, RIT>), dim3(runs / batches * a.n_list, T), dim3(256), 0, st, a,
+                     batches);
+}
+
 static bool dispatch_gateup(const FfnArgs& a, int T, hipStream_t st, hipEvent_t ps,
                             hipEvent_t pe) {
   switch (a.d) {
@@ -749,11 +986,17 @@ static bool dispatch_gateup(const FfnArgs& a, int T, hipStream_t st, hipEvent_t 
   return false;
 }
 
+static bool dispatch_hdown(const FfnArgs& a, int T, hipStream_t st) {
+  switch (a.I) {
+    case 256: hdown<8, 1>(a, T, st); return true;
+    case 512: hdown<16, 1>(a, T, st); return true;
+    case 1024: hdown<32, 1>(a, T, st); return true;
+  }
+  return false;
+}
+
 static bool dispatch_down(const FfnArgs& a, int T, hipStream_t st) {
   switch (a.I) {
-    case 256: down<8, 1>(a, T, st); return true;
-    case 512: down<16, 1>(a, T, st); return true;
-    case 1024: down<32, 1>(a, T, st); return true;
     case 2048: down<64, 1>(a, T, st); return true;
     case 4096: down<64, 2>(a, T, st); return true;
     case 8192: down<64, 4>(a, T, st); return true;
@@ -761,11 +1004,14 @@ static bool dispatch_down(const FfnArgs& a, int T, hipStream_t st) {
   return false;
 }
 
+// h and down in one launch up to I = 1024; beyond that a workgroup's own copy of
+// h would be more work than its rows, and h gets a launch of its own.
 hipError_t launch_ffn(const FfnArgs& a, int T, hipStream_t st, hipEvent_t prof_start,
                       hipEvent_t prof_stop) {
   if (!dispatch_gateup(a, T, st, prof_start, prof_stop)) return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (dispatch_hdown(a, T, st)) return hipGetLastError();
   hipLaunchKernelGGL(ffn_h_kernel, dim3((a.I >> 6) * a.n_list, T), dim3(64), 0, st, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
