@@ -11,6 +11,7 @@
 // rows with fully coalesced 16-byte loads.  A lane's chunks are the same for
 // every row it visits, so the 32*CPL activations it needs stay in registers.
 #include <algorithm>
+#include <type_traits>
 
 #include "moe_kernels.h"
 #include "moe_xchg.h"
@@ -771,19 +772,43 @@ __global__ void __launch_bounds__(256) ffn_hdown_kernel(FfnArgs a, int batches) 
 // ------------------------------------------------------------------------
 // Combine: y = sum_k w_k y_k + sum_s y_shared_s.
 // ------------------------------------------------------------------------
+// (four columns a thread, the loads of up to eight experts at once: one after the
+// other, each waits for the expert kernel's writes in another XCD's L2 at T = 1)
 __global__ void __launch_bounds__(256) combine_kernel(const float* __restrict__ ye,
                                                       const float* __restrict__ w, int K, int S,
                                                       int d, float* __restrict__ y, int accumulate) {
   const int t = blockIdx.y;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  const int j = 4 * (blockIdx.x * blockDim.x + threadIdx.x);
   if (j >= d) return;
   const int n = K + S;
   const float* base = ye + (size_t)t * n * d + j;
-  float acc = 0.f;
-  for (int k = 0; k < K; ++k) acc = fmaf(w[(size_t)t * K + k], base[(size_t)k * d], acc);
-  for (int s = 0; s < S; ++s) acc += base[(size_t)(K + s) * d];
-  float* out = y + (size_t)t * d + j;
-  *out = accumulate ? *out + acc : acc;
+  const float* wt = w + (size_t)t * K;
+  float4* out = reinterpret_cast<float4*>(y + (size_t)t * d + j);
+  float4 old = {0.f, 0.f, 0.f, 0.f}, acc = {0.f, 0.f, 0.f, 0.f};
+  if (accumulate) old = *out;
+  auto group = [&](int k0, auto count) {
+    constexpr int C = decltype(count)::value;
+    float4 v[C];
+#pragma unroll
+    for (int q = 0; q < C; ++q) v[q] = *reinterpret_cast<const float4*>(base + (size_t)(k0 + q) * d);
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      const float f = k0 + q < K ? wt[k0 + q] : 1.f;  // (1 x v + acc is acc + v)
+      acc.x = fmaf(f, v[q].x, acc.x);
+      acc.y = fmaf(f, v[q].y, acc.y);
+      acc.z = fmaf(f, v[q].z, acc.z);
+      acc.w = fmaf(f, v[q].w, acc.w);
+    }
+  };
+  int k0 = 0;
+  for (; k0 + 8 <= n; k0 += 8) group(k0, std::integral_constant<int, 8>());
+  if (k0 + 4 <= n) {
+    group(k0, std::integral_constant<int, 4>());
+    k0 += 4;
+  }
+  for (; k0 < n; ++k0) group(k0, std::integral_constant<int, 1>());
+  if (accumulate) acc = float4{old.x + acc.x, old.y + acc.y, old.z + acc.z, old.w + acc.w};
+  *out = acc;
 }
 
 // ------------------------------------------------------------------------
@@ -1021,8 +1046,9 @@ hipError_t launch_ffn(const FfnArgs& a, int T, hipStream_t st, hipEvent_t prof_s
 
 hipError_t launch_combine(const float* ye, const float* w, int T, int K, int S, int d, float* y,
                           int accumulate, hipStream_t st) {
-  hipLaunchKernelGGL(combine_kernel, dim3((d + 255) / 256, T), dim3(256), 0, st, ye, w, K, S, d, y,
-                     accumulate);
+  const int threads = T >= 64 ? 256 : 64;        // (d is a multiple of 512)
+  hipLaunchKernelGGL(combine_kernel, dim3((d / 4 + threads - 1) / threads, T), dim3(threads), 0, st, ye, w, K, S, d,
+                     y, accumulate);
   return hipGetLastError();
 }
 
