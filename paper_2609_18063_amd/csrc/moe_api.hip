@@ -30,6 +30,7 @@ bool pow2_dim(int v) {
 struct WsLayout {
   size_t logits, gx, ux, h, ag, au, adpart;
   size_t g_perm, g_tiles, g_tok, g_ntiles, g_h, g_xp, g_ax, g_adp;  // grouped (batched) path
+  moe::GroupedPlan g_plan;
   int g_max_tiles;
   size_t total;
 };
@@ -51,14 +52,15 @@ WsLayout ws_layout(const moe_layer_spec* s, int T) {
   w.ag = take((size_t)T * n * r * sizeof(float));
   w.au = take((size_t)T * n * r * sizeof(float));
   w.adpart = take((size_t)T * n * (s->d_expert / 64) * r * sizeof(float));
-  w.g_max_tiles = moe::grouped_max_tiles(T, (int)n, s->n_experts + s->n_shared);
+  w.g_plan = moe::grouped_plan(T, s->d_model, s->d_expert, s->n_experts, s->top_k, s->n_shared);
+  w.g_max_tiles = moe::grouped_max_tiles(T, (int)n, s->n_experts + s->n_shared, w.g_plan.tile_rows);
   w.g_perm = take((size_t)T * n * sizeof(int32_t));
   w.g_tiles = take((size_t)w.g_max_tiles * sizeof(moe::GroupTile));
-  w.g_tok = take((size_t)w.g_max_tiles * moe::kGroupRows * sizeof(int32_t));
+  w.g_tok = take((size_t)w.g_max_tiles * w.g_plan.tile_rows * sizeof(int32_t));
   w.g_ntiles = take(sizeof(int32_t));
   w.g_h = take((size_t)T * n * s->d_expert * sizeof(__half));
   w.g_xp = take((size_t)T * s->d_model * sizeof(__half));
-  w.g_ax = take((size_t)T * n * 4 * 2 * 16 * sizeof(float));
+  w.g_ax = take((size_t)T * n * w.g_plan.splits * 2 * 16 * sizeof(float));
   w.g_adp = take((size_t)T * n * (s->d_expert / moe::kGroupSlab > 0 ? s->d_expert / moe::kGroupSlab : 1) * 16 * sizeof(float));
   w.total = off;
   return w;
@@ -447,6 +449,9 @@ int moe_expert_ffn_grouped_int4_lora(const moe_layer_spec* s, const moe_slot_tab
   a.tile_tok = at<int32_t>(ws, L.g_tok);
   a.n_tiles = at<int32_t>(ws, L.g_ntiles);
   a.max_tiles = L.g_max_tiles;
+  a.wide = L.g_plan.wide;
+  a.tile_rows = L.g_plan.tile_rows;
+  a.splits = L.g_plan.splits;
   a.h = at<__half>(ws, L.g_h);
   a.xp = at<__half>(ws, L.g_xp);
   a.ax = at<float>(ws, L.g_ax);

@@ -7,10 +7,9 @@
 
 namespace moe {
 
-constexpr int kGroupRows = 64;   // permuted rows per tile (4 MFMA row blocks of 16)
 constexpr int kGroupMaxR = 16;   // LoRA rank the grouped path supports
 constexpr int kGroupMaxG = 2048; // experts + shared experts the permutation handles
-constexpr int kGroupSlab = 64;   // columns of one partial A_d h (one gate/up workgroup)
+constexpr int kGroupSlab = 64;   // the fewest columns of one partial A_d h (one gate/up workgroup)
 
 // One tile of the grouped GEMMs: rows [row0, row0 + nrows) of the permuted
 // list, all routed to group g (expert id g < E, shared expert E + s), whose
@@ -24,6 +23,7 @@ struct GroupTile {
 
 struct GroupedArgs {
   int T, d, I, E, K, S, r, n_list, n_ids;
+  int wide, tile_rows, splits;  // grouped_plan
   float lora_scale;
   const __half* x;              // [T][d]
   const int32_t* idx;           // [T][K]
@@ -33,21 +33,28 @@ struct GroupedArgs {
   // workspace
   int32_t* perm;                // [T * n_list]: y_experts row (t * n_list + k) of each position
   GroupTile* tiles;             // [max_tiles]
-  int32_t* tile_tok;            // [max_tiles][kGroupRows]: token of each tile row (unset
+  int32_t* tile_tok;            // [max_tiles][tile_rows]: token of each tile row (unset
                                 // past nrows)
   int32_t* n_tiles;             // [1]
   int max_tiles;
   __half* h;                    // [T * n_list][I], by permuted position, pair order
   __half* xp;                   // [T][d]: x in pair order
-  float* ax;                    // [T * n_list][4][2][16]: A_g x, A_u x by permuted position,
-                                // per quarter of d
-  float* adp;                   // [T * n_list][I / kGroupSlab][16]: A_d h over column slabs
+  float* ax;                    // [T * n_list][splits][2][16]: A_g x, A_u x by permuted position,
+                                // per part of d
+  float* adp;                   // [T * n_list][slabs][16]: A_d h over column slabs
   float* y_experts;             // [T][n_list][d]
 };
 
-// Upper bound on the tiles of T tokens: sum over groups of ceil(m_g / 64).
-inline int grouped_max_tiles(int T, int n_list, int groups) {
-  return (T * n_list + kGroupRows - 1) / kGroupRows + groups;
+// Which gate/up shape a call takes, its token rows per tile, and the parts of d
+// in which A x is formed.
+struct GroupedPlan {
+  int wide, tile_rows, splits;
+};
+GroupedPlan grouped_plan(int T, int d, int I, int E, int K, int S);
+
+// Upper bound on the tiles of T tokens: sum over groups of ceil(m_g / rows).
+inline int grouped_max_tiles(int T, int n_list, int groups, int rows) {
+  return (T * n_list + rows - 1) / rows + groups;
 }
 
 bool grouped_shape_supported(int d, int I, int r, int groups);
