@@ -75,15 +75,14 @@ class DeviceChain:
             if self.uses_prediction(t, n):
                 idx, w = self.pred_idx[t % 2, n], self.pred_w[t % 2, n]
             else:
-                B.route(s, self.x, lay["router"], self.own_idx, self.own_w, self.ws)
-                idx, w = self.own_idx, self.own_w
+                idx, w = self.own_idx if self.heads_mlp is None else self.used_idx[t % 2, n], self.own_w
+                B.route(s, self.x, lay["router"], idx, w, self.ws)
             mlp = self.heads_mlp[n] if self.heads_mlp is not None else None
             if n + 1 < self.L and mlp is not None:
                 nxt = (t + 1) % 2
                 prev = self.used_idx[(t - 1) % 2, n] if t > 0 else None
                 B.preroute_mlp(s, mlp, self.x, idx, prev, self.pred_idx[nxt, n + 1], self.pred_w[nxt, n + 1],
                                self.ws_mlp)
-                self.used_idx[t % 2, n].copy_(idx)
             elif n + 1 < self.L and lay.get("head") is not None:
                 nxt = (t + 1) % 2
                 B.preroute(s, self.x, lay["head"], self.pred_idx[nxt, n + 1], self.pred_w[nxt, n + 1],
@@ -100,6 +99,23 @@ class DeviceChain:
                     nxt = (t + 1) % 2
                     record["pidx"][t, n].copy_(self.pred_idx[nxt, n + 1, 0])
                     record["pw"][t, n].copy_(self.pred_w[nxt, n + 1, 0])
+
+        if self.heads_mlp is not None:
+            self._keep_used(t)
+
+    def _keep_used(self, t):
+        """The predictions that token ``t`` routed by, for the heads of the next
+        token. They stay in ``pred_idx`` until the heads of token t + 1 write
+        there, so runs of layers are kept with one copy each at the token's end
+        (own routing went to ``used_idx`` directly)."""
+        n = 0
+        while n < self.L:
+            m = n
+            while m < self.L and self.uses_prediction(t, m):
+                m += 1
+            if m > n:
+                self.used_idx[t % 2, n:m].copy_(self.pred_idx[t % 2, n:m])
+            n = m + 1
 
     def reset(self):
         self.r.zero_()
