@@ -158,4 +158,50 @@ __device__ __forceinline__ float topk_key_value(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
+// Softmax-top-k of one token's logits by one wave (K <= 32, E <= 64 V). Selection
+// is on the fp32 logits (the softmax is increasing), descending, ties to the lower
+// index; weights are the softmax renormalized over the selected set. Lane l holds
+// the V logits l V .. l V + V - 1 as order keys; each of K rounds takes the largest
+// key left over the wave (ties: the lowest lane, then its lowest position, which is
+// the lowest id). A round is a dozen lane moves: no barrier and no LDS.
+template <int V>
+__device__ __forceinline__ void wave_topk(const float* l, int E, int K, int32_t* idx, float* w) {
+  const int lane = threadIdx.x & 63;
+  uint32_t key[V];                               // 0: no logit, or taken (no real key is 0)
+#pragma unroll
+  for (int j = 0; j < V; ++j) key[j] = lane * V + j < E ? topk_key(l[lane * V + j]) : 0u;
+  uint32_t best = key[0];
+#pragma unroll
+  for (int j = 1; j < V; ++j) best = max(best, key[j]);
+  uint32_t mk = 0;                               // lane k: the k-th largest key and its id
+  int mi = 0;
+  for (int k = 0; k < K; ++k) {
+    const uint32_t m = wave_max_u32(best);
+    const int win = __builtin_ctzll(__ballot(best == m));
+    int pos = V - 1;
+#pragma unroll
+    for (int j = V - 2; j >= 0; --j) pos = key[j] == m ? j : pos;
+    const int id = __builtin_amdgcn_readlane(pos, win) + win * V;
+    if (lane == k) {
+      mk = m;
+      mi = id;
+    }
+    uint32_t nb = 0;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      key[j] = lane == win && j == pos ? 0u : key[j];
+      nb = max(nb, key[j]);
+    }
+    best = nb;
+  }
+  const float v = lane < K ? topk_key_value(mk) : 0.f;
+  const float mx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
+  const float ex = lane < K ? expf(v - mx) : 0.f;
+  const float sum = wave_sum(ex);
+  if (lane < K) {
+    idx[lane] = mi;
+    w[lane] = ex / sum;
+  }
+}
+
 }  // namespace moe

@@ -366,8 +366,8 @@ __global__ void __launch_bounds__(NT) pipe_kernel(EngineArgs) {
     if constexpr (SIG)
       eng::block_topk_sigmoid_group(l, nullptr, E, K, apx->n_groups, apx->top_groups, apx->route_scale, idx_out, w_out,
                                     tk_sig, tk_keys, tk_part, tk_cand, tk_sorted);
-    else
-      block_topk(l, E, K, idx_out, w_out, tk_keys, tk_part, tk_cand, tk_sorted);
+    else if (wave == 0)
+      wave_topk<(SH::EX + 63) / 64>(l, E, K, idx_out, w_out);
   };
   const int n_list = K + apx->S;
   const int GX = n_list * IE / NXG;

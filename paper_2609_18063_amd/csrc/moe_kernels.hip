@@ -197,54 +197,15 @@ __global__ void __launch_bounds__(64 * kRouteWaves) route_mfma_kernel(const __ha
   }
 }
 
-// Softmax-top-k, one wave per token. Lane l holds the V logits l V .. l V + V - 1
-// as order keys; each of K rounds takes the largest key left over the wave
-// (ties: the lowest lane, then its lowest position, which is the lowest id). A
-// round is a dozen lane moves, so K <= 32 rounds need no barrier and no LDS:
-// 2.5 - 3.3 us a call up to T = 777 and 4.6 us at T = 3100 (E 256, K 8); one
-// 512-thread workgroup per token took 8.8 us there. For E 1000, 6.7 us; a wave
-// finding the K-th key bit by bit took 17 us.
+// One wave per token: 2.5 - 3.3 us a call up to T = 777 and 4.6 us at T = 3100
+// (E 256, K 8); one 512-thread workgroup per token took 8.8 us there. For E 1000,
+// 6.7 us; a wave finding the K-th key bit by bit took 17 us.
 template <int V>
 __global__ void __launch_bounds__(256) topk_wave_kernel(const float* __restrict__ logits, int T, int E, int K,
                                                         int32_t* __restrict__ idx, float* __restrict__ w) {
-  const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (t >= T) return;
-  const float* l = logits + (size_t)t * E;
-  uint32_t key[V];                               // 0: no logit, or taken (no real key is 0)
-#pragma unroll
-  for (int j = 0; j < V; ++j) key[j] = lane * V + j < E ? topk_key(l[lane * V + j]) : 0u;
-  uint32_t best = key[0];
-#pragma unroll
-  for (int j = 1; j < V; ++j) best = max(best, key[j]);
-  uint32_t mk = 0;                               // lane k: the k-th largest key and its id
-  int mi = 0;
-  for (int k = 0; k < K; ++k) {
-    const uint32_t m = wave_max_u32(best);
-    const int win = __builtin_ctzll(__ballot(best == m));
-    int pos = V - 1;
-#pragma unroll
-    for (int j = V - 2; j >= 0; --j) pos = key[j] == m ? j : pos;
-    const int id = __builtin_amdgcn_readlane(pos, win) + win * V;
-    if (lane == k) {
-      mk = m;
-      mi = id;
-    }
-    uint32_t nb = 0;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      key[j] = lane == win && j == pos ? 0u : key[j];
-      nb = max(nb, key[j]);
-    }
-    best = nb;
-  }
-  const float v = lane < K ? topk_key_value(mk) : 0.f;
-  const float mx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
-  const float ex = lane < K ? expf(v - mx) : 0.f;
-  const float sum = wave_sum(ex);
-  if (lane < K) {
-    idx[(size_t)t * K + lane] = mi;
-    w[(size_t)t * K + lane] = ex / sum;
-  }
+  wave_topk<V>(logits + (size_t)t * E, E, K, idx + (size_t)t * K, w + (size_t)t * K);
 }
 
 // Sigmoid-group selection (App. A), one 512-thread workgroup per token
