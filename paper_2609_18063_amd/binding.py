@@ -176,14 +176,27 @@ def _check(rc, what):
     return rc
 
 
+# A call at T = 1 costs the host more than the GPU (its kernels are a few us each), so
+# addresses go to ctypes as plain integers and the current stream is read without
+# building a Stream object.
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_torch = None
 
 
 def _stream(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    global _torch
+    if stream is not None:
+        return stream.cuda_stream
+    if _torch is None:
+        import torch
+        _torch = torch
+    if not _torch.cuda.is_initialized():
+        return _torch.cuda.current_stream().cuda_stream
+    return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
 
 
 class StreamPair:
@@ -425,7 +438,7 @@ def rmsnorm_f16(xi, x, stream=None):
 def route(spec, x, w_router, idx, w, workspace, logits=None, stream=None):
     T = x.shape[0]
     _check(lib().moe_route(ctypes.byref(spec), _ptr(x), _ptr(w_router), T, _ptr(logits), _ptr(idx),
-                           _ptr(w), _ptr(workspace), workspace.numel() * workspace.element_size(),
+                           _ptr(w), _ptr(workspace), workspace.nbytes,
                            _stream(stream)), "moe_route")
 
 
@@ -433,7 +446,7 @@ def preroute(spec_next, x, w_head, pred_idx, pred_w, workspace, logits=None, str
     T = x.shape[0]
     _check(lib().moe_preroute(ctypes.byref(spec_next), _ptr(x), _ptr(w_head), T, _ptr(logits),
                               _ptr(pred_idx), _ptr(pred_w), _ptr(workspace),
-                              workspace.numel() * workspace.element_size(), _stream(stream)),
+                              workspace.nbytes, _stream(stream)),
            "moe_preroute")
 
 
@@ -454,7 +467,7 @@ def preroute_mlp(spec_next, head, x, routed_t, routed_tm1, pred_idx, pred_w, wor
     T = x.shape[0]
     _check(lib().moe_preroute_mlp(ctypes.byref(spec_next), ctypes.byref(head), _ptr(x), T, _ptr(routed_t),
                                   _ptr(routed_tm1), _ptr(logits), _ptr(pred_idx), _ptr(pred_w),
-                                  _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                  _ptr(workspace), workspace.nbytes,
                                   _stream(stream)), "moe_preroute_mlp")
 
 
@@ -462,7 +475,7 @@ def expert_ffn(spec, table, layer, x, idx, y_experts, status, workspace, stream=
     T = x.shape[0]
     _check(lib().moe_expert_ffn_int4_lora(ctypes.byref(spec), table.handle, layer, _ptr(x), T,
                                           _ptr(idx), _ptr(y_experts), _ptr(status), _ptr(workspace),
-                                          workspace.numel() * workspace.element_size(),
+                                          workspace.nbytes,
                                           _stream(stream)), "moe_expert_ffn_int4_lora")
 
 
@@ -484,7 +497,7 @@ def expert_ffn_grouped(spec, table, layer, x, idx, y_experts, status, workspace,
     _check(lib().moe_expert_ffn_grouped_int4_lora(ctypes.byref(spec), table.handle, layer, _ptr(x),
                                                   T, _ptr(idx), _ptr(y_experts), _ptr(status),
                                                   _ptr(workspace),
-                                                  workspace.numel() * workspace.element_size(),
+                                                  workspace.nbytes,
                                                   _stream(stream)),
            "moe_expert_ffn_grouped_int4_lora")
 
@@ -590,7 +603,7 @@ def engine_layers(spec, table, layer_arr, step_layer, xi, y, workspace, idx=None
     _check(lib().moe_engine_layers(ctypes.byref(spec), table.handle, _ptr(layer_arr),
                                    _ptr(step_layer), n, _ptr(xi), _ptr(y), _ptr(idx), _ptr(w),
                                    _ptr(pidx), _ptr(pw), _ptr(status), _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream(stream)),
+                                   workspace.nbytes, _stream(stream)),
            "moe_engine_layers")
 
 
@@ -605,7 +618,7 @@ def engine_tokens(spec, table, layer_arr, step_layer, xi, y, workspace, idx=None
     _check(lib().moe_engine_tokens(ctypes.byref(spec), table.handle, _ptr(layer_arr),
                                    _ptr(step_layer), n, _ptr(xi), _ptr(y), _ptr(idx), _ptr(w),
                                    _ptr(pidx), _ptr(pw), _ptr(status), _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream(stream)),
+                                   workspace.nbytes, _stream(stream)),
            "moe_engine_tokens")
 
 
@@ -618,7 +631,7 @@ def engine_chain(spec, table, layer_arr, n_layers, first_token, xi, r_state, wor
                                   _ptr(r_rec), _ptr(idx), _ptr(w), _ptr(pidx), _ptr(pw),
                                   _ptr(y_rec),
                                   _ptr(status), _ptr(workspace),
-                                  workspace.numel() * workspace.element_size(), _stream(stream)),
+                                  workspace.nbytes, _stream(stream)),
            "moe_engine_chain")
 
 
@@ -632,5 +645,5 @@ def engine_chain_mlp(spec, table, layer_arr, head_arr, hidden, n_layers, first_t
                                       int(hidden), n_layers, first_token, n_tokens, _ptr(xi), _ptr(r_state),
                                       _ptr(x_rec), _ptr(r_rec), _ptr(idx), _ptr(w), _ptr(pidx), _ptr(pw),
                                       _ptr(y_rec), _ptr(status), _ptr(workspace),
-                                      workspace.numel() * workspace.element_size(), _stream(stream)),
+                                      workspace.nbytes, _stream(stream)),
            "moe_engine_chain_mlp")
