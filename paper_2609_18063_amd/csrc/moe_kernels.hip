@@ -513,9 +513,9 @@ __global__ void __launch_bounds__(256) ffn_down_kernel(FfnArgs a) {
 // (LoRA-B of gate / up, SwiGLU) and A_down h in LDS, then its output rows. The
 // operands that do not depend on h (gate / up sums, LoRA rows, the workgroup's
 // codes) are requested before the first barrier, so the three phases wait for
-// memory once. Both launches of a call, K + S 9, d 2048, I 512: 15.1 us at T = 1
-// and 104.6 at T = 24 (three launches: 26.3 and 141); K 4, d 4096, I 1024: 23.1 and
-// 170 us (32.4 and 227). Latency-bound at T = 1; passing the resolved bundle on
+// memory once. Both launches of a call, K + S 9, d 2048, I 512: 15.3 us at T = 1
+// and 105 at T = 24 (three launches: 26.2 and 141); K 4, d 4096, I 1024: 23.8 and
+// 172 us (32.6 and 226). Latency-bound at T = 1; passing the resolved bundle on
 // from the first launch changed nothing (15.1 and 15.5 us).
 // ------------------------------------------------------------------------
 
@@ -657,30 +657,36 @@ __global__ void __launch_bounds__(256) ffn_hdown_kernel(FfnArgs a, int batches) 
   if (has_lora) {
     for (int m = 0; wave + 4 * m < a.r; ++m) {
       const int kk = wave + 4 * m;
+      // a 64-element slice is eight lanes' pieces, its products added as a balanced
+      // tree; the slices are added in order (the sums of the separate h launch, bit
+      // for bit)
       float s = 0.f;
 #pragma unroll
       for (int q = 0; q < PQ; ++q) {
+#pragma clang fp contract(off)
         const int c = lane + kWave * q;
+        float v = 0.f;
         if (c < I / 8) {
-          U4 v = {0, 0, 0, 0};
+          U4 a8 = {0, 0, 0, 0};
           if (m < RW) {
 #pragma unroll
             for (int z = 0; z < RW; ++z)
-              if (m == z) v = ar[z][q];
+              if (m == z) a8 = ar[z][q];
           } else {
-            v = ld16(al + (size_t)kk * I + 8 * c);
+            a8 = ld16(al + (size_t)kk * I + 8 * c);
           }
           const float* hp = hs + (c >> 2) * 36 + (c & 3) * 8;
-          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float2 f = h2f2(w[i]);
-            s = fmaf(f.x, hp[2 * i], s);
-            s = fmaf(f.y, hp[2 * i + 1], s);
-          }
+          const float2 f0 = h2f2(a8.x), f1 = h2f2(a8.y), f2 = h2f2(a8.z), f3 = h2f2(a8.w);
+          v = ((f0.x * hp[0] + f0.y * hp[1]) + (f1.x * hp[2] + f1.y * hp[3])) +
+              ((f2.x * hp[4] + f2.y * hp[5]) + (f3.x * hp[6] + f3.y * hp[7]));
         }
+        v += dpp_f<0xB1>(0.f, v);
+        v += dpp_f<0x4E>(0.f, v);
+        v += dpp_f<0x141>(0.f, v);
+#pragma unroll
+        for (int sl = 0; sl < 8; ++sl)
+          if (8 * q + sl < I / 64) s += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 8 * sl));
       }
-      s = wave_sum(s);
       if (lane == 0) ad[kk] = s;
     }
   }
