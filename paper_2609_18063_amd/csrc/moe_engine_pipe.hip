@@ -43,7 +43,6 @@
 namespace moe {
 namespace pipe {
 
-using eng::block_topk;
 using eng::claim_place;
 using eng::dma16;
 using eng::dma4;
