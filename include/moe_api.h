@@ -151,8 +151,9 @@ int moe_slot_table_sync(moe_slot_table* t, void* stream);
 int moe_rmsnorm_f16(const float* xi, int T, int d, void* x_f16, void* stream);
 
 /* Workspace bytes needed by moe_route / moe_preroute / moe_expert_ffn_int4_lora
- * for T tokens. The caller allocates it (no initial contents needed). Calls that
- * share one workspace must be ordered on one stream. */
+ * / moe_expert_ffn_grouped_int4_lora for T tokens. It grows with T: a workspace for
+ * the most tokens serves every smaller call. The caller allocates it (no initial
+ * contents needed). Calls that share one workspace must be ordered on one stream. */
 size_t moe_workspace_bytes(const moe_layer_spec* spec, int T);
 
 /*

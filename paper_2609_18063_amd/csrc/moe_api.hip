@@ -54,9 +54,14 @@ WsLayout ws_layout(const moe_layer_spec* s, int T) {
   w.adpart = take((size_t)T * n * (s->d_expert / 64) * r * sizeof(float));
   w.g_plan = moe::grouped_plan(T, s->d_model, s->d_expert, s->n_experts, s->top_k, s->n_shared);
   w.g_max_tiles = moe::grouped_max_tiles(T, (int)n, s->n_experts + s->n_shared, w.g_plan.tile_rows);
+  // The wide plan has half as many tile records and up to twice the padding in its token
+  // lists. Each array takes the larger of the two plans' needs, so that the layout only
+  // grows with T and a workspace for the most tokens serves every smaller call.
+  const int most = moe::grouped_max_tiles(T, (int)n, s->n_experts + s->n_shared, moe::kGroupMinRows);
   w.g_perm = take((size_t)T * n * sizeof(int32_t));
-  w.g_tiles = take((size_t)w.g_max_tiles * sizeof(moe::GroupTile));
-  w.g_tok = take((size_t)w.g_max_tiles * w.g_plan.tile_rows * sizeof(int32_t));
+  w.g_tiles = take((size_t)std::max(w.g_max_tiles, most) * sizeof(moe::GroupTile));
+  w.g_tok = take(std::max((size_t)w.g_max_tiles * w.g_plan.tile_rows, (size_t)most * moe::kGroupMinRows) *
+                 sizeof(int32_t));
   w.g_ntiles = take(sizeof(int32_t));
   w.g_h = take((size_t)T * n * s->d_expert * sizeof(__half));
   w.g_xp = take((size_t)T * s->d_model * sizeof(__half));

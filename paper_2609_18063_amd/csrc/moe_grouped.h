@@ -9,6 +9,7 @@ namespace moe {
 
 constexpr int kGroupMaxR = 16;   // LoRA rank the grouped path supports
 constexpr int kGroupMaxG = 2048; // experts + shared experts the permutation handles
+constexpr int kGroupMinRows = 64; // token rows of a tile in the narrow plan
 constexpr int kGroupSlab = 64;   // the fewest columns of one partial A_d h (one gate/up workgroup)
 
 // One tile of the grouped GEMMs: rows [row0, row0 + nrows) of the permuted

@@ -93,6 +93,7 @@ struct Shape {
   static constexpr int TR = 16 * V::TRB;           // token rows of a tile
   static constexpr int XJ = V::TRB / 2;            // activation copies of a wave per chunk, at most
 };
+static_assert(Shape<GateNarrow>::TR == kGroupMinRows && Shape<GateNarrow>::GATE == kGroupSlab, "workspace layout");
 // (s, z) rows of a workgroup's weight rows, staged once per tile: k / 16 bytes a row
 template <class V>
 constexpr int lds_bytes(int k) {

@@ -250,3 +250,22 @@ def test_noalloc_ffn_rejects_sizes_beyond_its_scratch(B):
     rc = B.lib().moe_expert_ffn_int4_lora_noalloc(ctypes.byref(spec), None, 0, None, big, None,
                                                   None, None, None)
     assert rc == B.MOE_ENOMEM
+
+
+@pytest.mark.parametrize("d,I,E,K,S,r", [
+    (512, 256, 16, 2, 0, 8), (512, 256, 8, 1, 0, 0), (512, 256, 1, 1, 0, 64), (2048, 512, 256, 8, 1, 16),
+    (4096, 1024, 64, 4, 0, 16), (512, 8192, 12, 1, 2, 5)])
+def test_workspace_grows_with_the_token_count(B, d, I, E, K, S, r):
+    """A workspace sized for a token count serves every smaller one, across the count
+    at which the grouped experts take the wide gate/up shape: at least 64 rows a
+    routed expert, and rows / 128 (rounded down) times d_expert / 128 at least 256."""
+    spec = B.make_spec(d, E, K, S, I, r, 2.0 if r else 0.0)
+    def up(a, b):
+        return -(-a // b)
+
+    wide = max(up(64 * E, K), up(128 * up(256, I // 128), K + S))
+    at = sorted(set(range(1, 70)) | set(range(max(1, wide - 40), wide + 41)) | {2 * wide, 4 * wide})
+    sizes = [B.workspace_bytes(spec, T) for T in at]
+    assert sizes[0] > 0
+    for (Ta, a), (Tb, b) in zip(zip(at, sizes), zip(at[1:], sizes[1:])):
+        assert a <= b, (Ta, a, Tb, b)
