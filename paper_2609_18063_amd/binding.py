@@ -185,18 +185,38 @@ def _ptr(t):
 
 
 _torch = None
+_raw_stream = None
+
+
+def _public_stream():
+    return _torch.cuda.current_stream().cuda_stream
+
+
+def _stream_reader():
+    """How the current stream is read: torch's internal reader (0.2 us a call; 3.1 us
+    through a Stream object) where this torch has it and it agrees with the public one."""
+    c = _torch._C
+    try:
+        raw, device = c._cuda_getCurrentRawStream, c._cuda_getDevice
+        if raw(device()) == _public_stream():
+            return lambda: raw(device())
+    except (AttributeError, TypeError):
+        pass
+    return _public_stream
 
 
 def _stream(stream=None):
-    global _torch
+    global _torch, _raw_stream
     if stream is not None:
         return stream.cuda_stream
-    if _torch is None:
-        import torch
-        _torch = torch
-    if not _torch.cuda.is_initialized():
-        return _torch.cuda.current_stream().cuda_stream
-    return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+    if _raw_stream is None:
+        if _torch is None:
+            import torch
+            _torch = torch
+        if not _torch.cuda.is_initialized():
+            return _public_stream()
+        _raw_stream = _stream_reader()
+    return _raw_stream()
 
 
 class StreamPair:

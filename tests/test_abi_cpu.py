@@ -269,3 +269,28 @@ def test_workspace_grows_with_the_token_count(B, d, I, E, K, S, r):
     assert sizes[0] > 0
     for (Ta, a), (Tb, b) in zip(zip(at, sizes), zip(at[1:], sizes[1:])):
         assert a <= b, (Ta, a, Tb, b)
+
+
+@pytest.mark.parametrize("raw", ["absent", "other arguments", "another value", "present"])
+def test_current_stream_without_the_raw_reader(monkeypatch, raw):
+    """The calls take torch's current stream whether or not torch has the internal
+    function that reads it without a Stream object."""
+    import types
+    from paper_2609_18063_amd import binding
+    now = [0x70]
+
+    def two(device, more):
+        return now[0]
+
+    c = types.SimpleNamespace(_cuda_getDevice=lambda: 0)
+    if raw != "absent":
+        c._cuda_getCurrentRawStream = {"other arguments": two, "another value": lambda d: 0x90,
+                                       "present": lambda d: now[0]}[raw]
+    cuda = types.SimpleNamespace(is_initialized=lambda: True,
+                                 current_stream=lambda: types.SimpleNamespace(cuda_stream=now[0]))
+    monkeypatch.setattr(binding, "_torch", types.SimpleNamespace(cuda=cuda, _C=c))
+    monkeypatch.setattr(binding, "_raw_stream", None, raising=False)
+    for value in (0x70, 0x50, 0x0):
+        now[0] = value
+        assert binding._stream() == value
+    assert binding._stream(types.SimpleNamespace(cuda_stream=0x30)) == 0x30
