@@ -93,6 +93,9 @@ struct Shape {
   static constexpr int TR = 16 * V::TRB;           // token rows of a tile
   static constexpr int XJ = V::TRB / 2;            // activation copies of a wave per chunk, at most
 };
+static_assert(Shape<GateWide>::TR == 2 * Shape<DownWide>::TR && Shape<DownNarrow>::TR == Shape<DownWide>::TR &&
+                  Shape<GateNarrow>::TR == Shape<DownWide>::TR,
+              "a tile is one or two parts of the prep and down launches");
 static_assert(Shape<GateNarrow>::TR == kGroupMinRows && Shape<GateNarrow>::GATE == kGroupSlab, "workspace layout");
 // (s, z) rows of a workgroup's weight rows, staged once per tile: k / 16 bytes a row
 template <class V>
@@ -389,12 +392,19 @@ __global__ void __launch_bounds__(kPT) grouped_permute_kernel(GroupedArgs a, int
   __shared__ uint64_t wcls[kPT / 64];
   const int G = a.E + a.S, TR = a.tile_rows;
   const int TK = a.T * a.K;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // A small call is bound by the instructions (16 waves on one CU: one takes each SIMD
+  // 16 clocks), so a wave leaves out what it has no ids and no groups for: d 512, E 8 or
+  // 64, T = 4 .. 16 3.5 us a launch (5.3 with every wave going through all of it).
+  auto any_id = [&](int base, int j) { return base + kPT * j + 64 * wave < TK; };  // (uniform)
   int ev[kIds];
   auto load_ids = [&](int base) {
 #pragma unroll
     for (int j = 0; j < kIds; ++j) {
+      ev[j] = -1;
+      if (!any_id(base, j)) continue;
       const int i = base + tid + kPT * j;
-      ev[j] = i < TK ? a.idx[i] : -1;
+      if (i < TK) ev[j] = a.idx[i];
     }
   };
   for (int g = tid; g < G; g += kPT) cnt[g] = g >= a.E ? a.T : 0;
@@ -404,113 +414,130 @@ __global__ void __launch_bounds__(kPT) grouped_permute_kernel(GroupedArgs a, int
   for (int base = 0; base < TK; base += kPT * kIds) {
     if (base) load_ids(base);
 #pragma unroll
-    for (int j = 0; j < kIds; ++j)
+    for (int j = 0; j < kIds; ++j) {
+      if (!any_id(base, j)) break;
       if (ev[j] >= 0 && ev[j] < a.E) atomicAdd(&cnt[ev[j]], 1);
+    }
   }
   __syncthreads();
   // thread t owns groups 2t and 2t+1: their rows, full tiles, and the size class
   // 1 .. 4 of their last tile (one 16-bit counter per class)
+  const int nw = (G + 127) >> 7;                 // waves that own groups
+  const bool owner = wave < nw;
   const int g0 = 2 * tid, g1 = g0 + 1;
-  const int c0 = g0 < G ? cnt[g0] : 0, c1 = g1 < G ? cnt[g1] : 0;
-  const int f0 = c0 / TR, f1 = c1 / TR;
-  const int k0 = (4 * (c0 - f0 * TR) + TR - 1) / TR, k1 = (4 * (c1 - f1 * TR) + TR - 1) / TR;
-  const uint64_t p0 = k0 ? 1ull << (16 * (k0 - 1)) : 0, p1 = k1 ? 1ull << (16 * (k1 - 1)) : 0;
-  int sr = c0 + c1, sf = f0 + f1;
-  uint64_t sc = p0 + p1;
-  const int lane = tid & 63, wave = tid >> 6;
+  int c0 = 0, c1 = 0, f0 = 0, f1 = 0, k0 = 0, k1 = 0, sr = 0, sf = 0;
+  uint64_t p0 = 0, p1 = 0, sc = 0;
+  if (owner) {
+    const int sh = __builtin_ctz(TR);            // (a power of two)
+    c0 = g0 < G ? cnt[g0] : 0;
+    c1 = g1 < G ? cnt[g1] : 0;
+    f0 = c0 >> sh;
+    f1 = c1 >> sh;
+    k0 = (4 * (c0 - f0 * TR) + TR - 1) >> sh;
+    k1 = (4 * (c1 - f1 * TR) + TR - 1) >> sh;
+    p0 = k0 ? 1ull << (16 * (k0 - 1)) : 0;
+    p1 = k1 ? 1ull << (16 * (k1 - 1)) : 0;
+    sr = c0 + c1;
+    sf = f0 + f1;
+    sc = p0 + p1;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int r = __shfl_up(sr, o, 64), f = __shfl_up(sf, o, 64);
-    const uint64_t c = (uint64_t)__shfl_up((unsigned long long)sc, o, 64);
-    if (lane >= o) {
-      sr += r;
-      sf += f;
-      sc += c;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int r = __shfl_up(sr, o, 64), f = __shfl_up(sf, o, 64);
+      const uint64_t c = (uint64_t)__shfl_up((unsigned long long)sc, o, 64);
+      if (lane >= o) {
+        sr += r;
+        sf += f;
+        sc += c;
+      }
     }
-  }
-  if (lane == 63) {
-    wrows[wave] = sr;
-    wfull[wave] = sf;
-    wcls[wave] = sc;
+    if (lane == 63) {
+      wrows[wave] = sr;
+      wfull[wave] = sf;
+      wcls[wave] = sc;
+    }
   }
   __syncthreads();
-  int full_all = 0;
-  uint64_t cls_all = 0;
-#pragma unroll
-  for (int w = 0; w < kPT / 64; ++w) {
-    if (w < wave) {
-      sr += wrows[w];
-      sf += wfull[w];
-      sc += wcls[w];
+  int off0 = 0, off1 = 0, t0 = 0, t1 = 0, r0 = 0, r1 = 0;  // first rows, first full tiles, last tiles
+  if (owner) {
+    int full_all = 0;
+    uint64_t cls_all = 0;
+    for (int w = 0; w < nw; ++w) {
+      const int r = wrows[w], f = wfull[w];
+      const uint64_t c = wcls[w];
+      full_all += f;
+      cls_all += c;
+      sr += w < wave ? r : 0;
+      sf += w < wave ? f : 0;
+      sc += w < wave ? c : 0;
     }
-    full_all += wfull[w];
-    cls_all += wcls[w];
-  }
-  const int off0 = sr - c0 - c1, off1 = sr - c1;               // first rows
-  const int t0 = sf - f0 - f1, t1 = sf - f1;                   // first full tiles
-  const uint64_t b0 = sc - p0 - p1, b1 = sc - p1;              // last tiles of each class before
-  int cbase[5];                                                // first tile of class k
-  cbase[4] = full_all;
+    off0 = sr - c0 - c1;
+    off1 = sr - c1;
+    t0 = sf - f0 - f1;
+    t1 = sf - f1;
+    const uint64_t b0 = sc - p0 - p1, b1 = sc - p1;            // last tiles of each class before
+    int cbase[5];                                              // first tile of class k
+    cbase[4] = full_all;
 #pragma unroll
-  for (int k = 3; k >= 1; --k) cbase[k] = cbase[k + 1] + (int)((cls_all >> (16 * k)) & 0xffff);
-  auto rem_tile = [&](int k, uint64_t before) {
-    int t = 0;
+    for (int k = 3; k >= 1; --k) cbase[k] = cbase[k + 1] + (int)((cls_all >> (16 * k)) & 0xffff);
+    auto rem_tile = [&](int k, uint64_t before) {
+      int t = 0;
 #pragma unroll
-    for (int q = 1; q <= 4; ++q)
-      if (k == q) t = cbase[q] + (int)((before >> (16 * (q - 1))) & 0xffff);
-    return t;
-  };
-  const int r0 = rem_tile(k0, b0), r1 = rem_tile(k1, b1);
-  const bool mine = (tid & (np - 1)) == (int)blockIdx.x;
-  // the slots and bundles of both groups requested together (one dependent
-  // pair of loads for the thread); a group that is not resident copies slot 0's
-  // bundle (a table has at least one slot), which no kernel reads. The bundle
-  // moves as 12 pointer words (held in registers).
-  constexpr int kBW = (int)(sizeof(moe_bundle) / 8);
-  static_assert(sizeof(moe_bundle) == 8 * kBW && sizeof(GroupTile) == 16 + sizeof(moe_bundle), "record layout");
-  if (mine) {
-    const int s0 = g0 < G && c0 ? a.slot_of[g0] : -1, s1 = g1 < G && c1 ? a.slot_of[g1] : -1;
-    uint64_t w0[kBW], w1[kBW];
-    const uint64_t* q0 = reinterpret_cast<const uint64_t*>(a.bundles + (s0 > 0 ? s0 : 0));
-    const uint64_t* q1 = reinterpret_cast<const uint64_t*>(a.bundles + (s1 > 0 ? s1 : 0));
-#pragma unroll
-    for (int q = 0; q < kBW; ++q) {
-      w0[q] = q0[q];
-      w1[q] = q1[q];
-    }
-    auto emit = [&](int g, int c, int off, int nfull, int full, int rem, int slot, const uint64_t (&w)[kBW]) {
-      if (g >= G || c == 0) return;
-      if (slot < 0 && a.status) atomicOr(a.status, MOE_STATUS_SLOT_MISS);
-      for (int j = 0; j * TR < c; ++j) {
-        GroupTile* o = a.tiles + (j < nfull ? full + j : rem);
-        o->g = g;
-        o->row0 = off + TR * j;
-        o->nrows = min(TR, c - TR * j);
-        o->slot = slot;
-        uint64_t* ob = reinterpret_cast<uint64_t*>(&o->b);
-#pragma unroll
-        for (int q = 0; q < kBW; ++q) ob[q] = w[q];
-      }
+      for (int q = 1; q <= 4; ++q)
+        if (k == q) t = cbase[q] + (int)((before >> (16 * (q - 1))) & 0xffff);
+      return t;
     };
-    emit(g0, c0, off0, f0, t0, r0, s0, w0);
-    emit(g1, c1, off1, f1, t1, r1, s1, w1);
+    r0 = rem_tile(k0, b0);
+    r1 = rem_tile(k1, b1);
+    if (tid == 0 && blockIdx.x == 0) *a.n_tiles = cbase[1] + (int)(cls_all & 0xffff);
+    // the slots and bundles of both groups requested together (one dependent
+    // pair of loads for the thread); a group that is not resident copies slot 0's
+    // bundle (a table has at least one slot), which no kernel reads. The bundle
+    // moves as 12 pointer words (held in registers).
+    constexpr int kBW = (int)(sizeof(moe_bundle) / 8);
+    static_assert(sizeof(moe_bundle) == 8 * kBW && sizeof(GroupTile) == 16 + sizeof(moe_bundle), "record layout");
+    if ((tid & (np - 1)) == (int)blockIdx.x) {
+      const int s0 = g0 < G && c0 ? a.slot_of[g0] : -1, s1 = g1 < G && c1 ? a.slot_of[g1] : -1;
+      uint64_t w0[kBW], w1[kBW];
+      const uint64_t* q0 = reinterpret_cast<const uint64_t*>(a.bundles + (s0 > 0 ? s0 : 0));
+      const uint64_t* q1 = reinterpret_cast<const uint64_t*>(a.bundles + (s1 > 0 ? s1 : 0));
+#pragma unroll
+      for (int q = 0; q < kBW; ++q) {
+        w0[q] = q0[q];
+        w1[q] = q1[q];
+      }
+      auto emit = [&](int g, int c, int off, int nfull, int full, int rem, int slot, const uint64_t (&w)[kBW]) {
+        if (g >= G || c == 0) return;
+        if (slot < 0 && a.status) atomicOr(a.status, MOE_STATUS_SLOT_MISS);
+        for (int j = 0; j * TR < c; ++j) {
+          GroupTile* o = a.tiles + (j < nfull ? full + j : rem);
+          o->g = g;
+          o->row0 = off + TR * j;
+          o->nrows = min(TR, c - TR * j);
+          o->slot = slot;
+          uint64_t* ob = reinterpret_cast<uint64_t*>(&o->b);
+#pragma unroll
+          for (int q = 0; q < kBW; ++q) ob[q] = w[q];
+        }
+      };
+      emit(g0, c0, off0, f0, t0, r0, s0, w0);
+      emit(g1, c1, off1, f1, t1, r1, s1, w1);
+    }
+    // each thread read its own two counts only: they become the insertion cursors
+    if (g0 < G) {
+      cnt[g0] = off0;
+      goff[g0] = off0;
+      gfull[g0] = t0;
+      gnf[g0] = f0 * TR;
+      grem[g0] = r0;
+    }
+    if (g1 < G) {
+      cnt[g1] = off1;
+      goff[g1] = off1;
+      gfull[g1] = t1;
+      gnf[g1] = f1 * TR;
+      grem[g1] = r1;
+    }
   }
-  __syncthreads();  // every count is read: the array becomes the insertion cursors
-  if (g0 < G) {
-    cnt[g0] = off0;
-    goff[g0] = off0;
-    gfull[g0] = t0;
-    gnf[g0] = f0 * TR;
-    grem[g0] = r0;
-  }
-  if (g1 < G) {
-    cnt[g1] = off1;
-    goff[g1] = off1;
-    gfull[g1] = t1;
-    gnf[g1] = f1 * TR;
-    grem[g1] = r1;
-  }
-  if (tid == 0 && blockIdx.x == 0) *a.n_tiles = cbase[1] + (int)(cls_all & 0xffff);
   __syncthreads();
   auto place = [&](int g, int pos, int row, int t) {
     const int rel = pos - goff[g];
@@ -525,6 +552,7 @@ __global__ void __launch_bounds__(kPT) grouped_permute_kernel(GroupedArgs a, int
     if (TK > kPT * kIds) load_ids(base);         // (else they are still in registers)
 #pragma unroll
     for (int j = 0; j < kIds; ++j) {
+      if (!any_id(base, j)) break;
       const int i = base + tid + kPT * j, e = ev[j];
       if (i >= TK) continue;
       const int t = i / a.K, row = t * a.n_list + i - t * a.K;
@@ -555,8 +583,9 @@ __global__ void __launch_bounds__(kGT, 4) grouped_prep_kernel(GroupedArgs a) {
   const int tid = threadIdx.x;
   // (the first parts of all tiles, then the second: neighbours in a launch go to
   // different XCDs, and second parts are often empty)
-  const int per = a.max_tiles * a.splits;
-  const int ti = (blockIdx.x % per) / a.splits, Q = blockIdx.x % a.splits, r0 = (blockIdx.x / per) * kPrepRows;
+  const int per = a.max_tiles * a.splits, second = (int)blockIdx.x >= per;
+  const int b = blockIdx.x - second * per;
+  const int ti = b >> __builtin_ctz(a.splits), Q = b & (a.splits - 1), r0 = second * kPrepRows;
   const int wave = tid >> 6, lane = tid & 63, col = lane & 15, kq = lane >> 4;
   // the tokens of this lane's rows (the tile's token list, read beside the record)
   int tok[4];
@@ -837,8 +866,9 @@ __global__ void __launch_bounds__(kGT, V::EU) grouped_down_kernel(GroupedArgs a,
   int bx, by;
   tile_of_block(blockIdx.x, a.d / DOWN, bx, by);
   // (the first parts of all tiles, then the second, as in prep)
-  const int tix = bx % a.max_tiles, first = (bx / a.max_tiles) * TR;
-  if (first >= a.tile_rows) return;              // the grid is rounded up
+  const int second = bx >= a.max_tiles;          // (a tile is one or two parts)
+  const int tix = bx - second * a.max_tiles, first = second * TR;
+  if (first >= a.tile_rows || tix >= a.max_tiles) return;  // the grid is rounded up
   const GroupTile tl = a.tiles[tix];             // (read beside the count, as in gate/up)
   if (tix >= *a.n_tiles) return;
   const int nrows = min(TR, tl.nrows - first), row0 = tl.row0 + first;

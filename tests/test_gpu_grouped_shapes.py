@@ -96,3 +96,37 @@ def test_group_sizes(torch_cuda, counts, d, I, r, S, bad):
     diff = (ye - rows).abs().amax(-1) / torch.maximum(size, size[size > 0].median())
     assert float(diff.max()) <= TOL_REL_INF
     table.close()
+
+
+@pytest.mark.parametrize("E,S,K,T", [(7, 0, 7, 1), (124, 4, 1, 3), (125, 4, 8, 9), (300, 1, 4, 64), (1024, 4, 32, 2),
+                                     (1024, 4, 32, 33), (1024, 4, 32, 300)])
+def test_many_groups(torch_cuda, E, S, K, T):
+    """The permutation's waves own 128 groups each and take 64 of 1024 ids a step:
+    group counts around whole waves, fewer and more ids than one pass of them."""
+    from paper_2609_18063_amd import binding as B, weights as W
+    torch = torch_cuda
+    g = np.random.default_rng(E + K + T)
+    d, I, r = 512, 256, 8
+    bundles = [_bundle(g, d, I, r) for _ in range(8)]
+    buf, offs, _ = W.pack_host(bundles)
+    dev = W.upload(buf)
+    spec = B.make_spec(d, E, K, S, I, r, 2.0)
+    table = B.SlotTable(1, E + S, E + S)
+    W.bind_layer(table, 0, dev, [offs[e % 8] for e in range(E + S)], g.permutation(E + S))
+    table.sync()
+    x = torch.from_numpy(g.standard_normal((T, d)).astype(np.float16)).cuda()
+    idx = torch.from_numpy(np.stack([g.permutation(E)[:K] for _ in range(T)]).astype(np.int32)).cuda()
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    out = []
+    for ffn in (B.expert_ffn_grouped, B.expert_ffn):
+        ws = torch.full((B.workspace_bytes(spec, T),), 255, dtype=torch.uint8, device="cuda")
+        out.append(torch.full((T, K + S, d), float("nan"), device="cuda"))
+        ffn(spec, table, 0, x, idx, out[-1], status, ws)
+    torch.cuda.synchronize()
+    ye, rows = out
+    assert status.item() == 0
+    size = rows.abs().amax(-1)
+    # (the bound of test_group_sizes)
+    diff = (ye - rows).abs().amax(-1) / torch.maximum(size, size.median())
+    assert float(diff.max()) <= TOL_REL_INF
+    table.close()
