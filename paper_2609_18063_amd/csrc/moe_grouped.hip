@@ -46,6 +46,7 @@
 // activations (x, h) are kept in pair order and the codes need no shuffle.
 // Every output row depends only on its own input row, so the order of rows
 // inside a group does not change any result bit.
+#include <algorithm>
 #include <type_traits>
 
 #include "moe_grouped.h"
@@ -937,7 +938,15 @@ __global__ void __launch_bounds__(kGT, V::EU) grouped_down_kernel(GroupedArgs a,
     for (int sl = 0; sl < kPreSl; ++sl) v += adv[q][sl];
     if (ld && row < nrows && k < r) {
       const float* src = a.adp + (size_t)(row0 + row) * nsl * 16 + k;
-      for (int sl = kPreSl; sl < nsl; ++sl) v += src[sl * 16];
+      // (eight loads at once, added in slab order: d 512, I 1024, T = 8 9.5 us a launch, 10.1
+      // one after the other)
+      for (int s0 = kPreSl; s0 < nsl; s0 += 8) {
+        float w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) w[u] = s0 + u < nsl ? src[(s0 + u) * 16] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += w[u];
+      }
     }
     la[row][k] = (_Float16)(v * a.lora_scale);
   }
@@ -1009,6 +1018,20 @@ GroupedPlan grouped_plan(int T, int d, int I, int E, int K, int S) {
   return wide ? GroupedPlan{1, Shape<GateWide>::TR, splits} : GroupedPlan{0, Shape<GateNarrow>::TR, splits};
 }
 
+// Beyond d_expert 512 a 256-column down workgroup is a long one (8 chunks, and half of
+// the slab partials fetched after them): while the columns of all tiles are no more
+// workgroups than CUs, 128 columns are faster, as there are CUs for twice as many. Whole
+// calls, 256 / 128 columns, d_expert 1024: d 512, E 64, T = 8 25.7 / 24.0 us; d 2048,
+// E 16, K 2, T = 16 34.4 / 32.2; from about 300 workgroups on the other way (d 2048, E 64,
+// T = 64 68.0 / 70.9; d 4096, T = 8 62.9 / 65.9). Up to 512 they differ by less than the
+// empty workgroups of twice the grid (d 2048, I 512, E 256, T = 1 30.1 / 30.7). The tiles
+// are estimated as if the routing were even.
+constexpr int kDownNarrowFill = 256;
+static bool down_narrow(const GroupedArgs& a) {
+  const long long tiles = std::min((long long)a.T * a.K, (long long)a.E) + a.S + (long long)a.T * a.n_list / kGroupMinRows;
+  return a.I > 512 && tiles * (a.d / Shape<DownWide>::DOWN) <= kDownNarrowFill;
+}
+
 hipError_t launch_grouped_ffn(const GroupedArgs& a, hipStream_t st) {
   const int np = a.T * a.K <= 2048 ? 8 : 32;     // (powers of two)
   const size_t xw = (size_t)kPT * kXPieces * 8;   // elements of x per workgroup
@@ -1036,7 +1059,7 @@ hipError_t launch_grouped_ffn(const GroupedArgs& a, hipStream_t st) {
     launch_gateup<GateNarrow>(a, st);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (2 * lds_bytes<DownWide>(a.I) <= kLdsMax)
+  if (2 * lds_bytes<DownWide>(a.I) <= kLdsMax && !down_narrow(a))
     launch_down<DownWide>(a, st);
   else
     launch_down<DownNarrow>(a, st);

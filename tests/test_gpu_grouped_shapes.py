@@ -130,3 +130,12 @@ def test_many_groups(torch_cuda, E, S, K, T):
     diff = (ye - rows).abs().amax(-1) / torch.maximum(size, size.median())
     assert float(diff.max()) <= TOL_REL_INF
     table.close()
+
+
+@pytest.mark.parametrize("counts,d,I,r,S,bad", [
+    (NARROW, 512, 1024, 5, 1, True), (NARROW, 2048, 1024, 16, 1, False), ((1, 2), 4096, 1024, 16, 0, False),
+    (NARROW, 512, 2048, 3, 0, True)])
+def test_down_shapes(torch_cuda, counts, d, I, r, S, bad):
+    """d_expert 1024 takes 128 or 256 output columns by the number of workgroups, with
+    more slab partials of A_d h than are fetched before the k loop."""
+    test_group_sizes(torch_cuda, counts, d, I, r, S, bad)
