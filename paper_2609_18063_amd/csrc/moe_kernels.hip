@@ -954,13 +954,24 @@ static void down(const FfnArgs& a, int T, hipStream_t st) {
 // a CU), so that the h of a workgroup is formed for as many rows as it can be.
 // Whole calls with 512 / 1024 / 2048: d 4096, I 1024, K 4: T = 4 45 / 52 / 64 us,
 // T = 24 170 / 175 / 186; d 2048, I 512, K + S 9: T = 8 45 / 46.5 / 51.
+// At I = 1024 a CU holds two workgroups (192 registers a lane): 513 to 1023 of them are
+// a second round for a few, each with an h of its own, so up to four runs a workgroup
+// are taken where that leaves one round, and up to eight for 256 workgroups beyond
+// rank 32, whose h costs most. K + S 5, one run / this rule / h in a launch of its own:
+// d 4096, T = 1, r 5 29.9 / 25.2 / 26.7 us, r 64 77 / 41.6 / 65; d 2048, T = 2, r 16
+// 25.0 / 22.0 / 30.3; d 512, T = 8, r 64 80.5 / 41.8 / 56.
 constexpr int kHdownFill = 512;
 template <int LPR, int CPL>
 static void hdown(const FfnArgs& a, int T, hipStream_t st) {
   constexpr int RIT = 4;
   const int runs = a.d / (4 * RIT * (kWave / LPR));  // (d >= 512, a power of two: at least 4)
+  const long long all = (long long)runs * a.n_list * T;
   int batches = 1;
-  while (2 * batches <= runs && (long long)runs * a.n_list * T / (2 * batches) >= kHdownFill) batches *= 2;
+  while (2 * batches <= runs && all / (2 * batches) >= kHdownFill) batches *= 2;
+  if (32 * LPR * CPL > 512) {
+    const int resident = a.r > 32 ? 256 : 512, most = a.r > 32 ? 8 : 4;
+    while (2 * batches <= std::min(runs, most) && all / batches > resident) batches *= 2;
+  }
   hipLaunchKernelGGL((ffn_hdown_kernel<LPR, CPL, RIT>), dim3(runs / batches * a.n_list, T), dim3(256), 0, st, a,
                      batches);
 }

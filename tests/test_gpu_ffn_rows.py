@@ -68,3 +68,12 @@ def test_rows_against_oracle(torch_cuda, d, I, r, T):
             # stay far below 2^-24 sqrt(d + I) of the largest output
             assert rel_inf(got[t, k], ref) <= 4 * 2.0 ** -24 * np.sqrt(d + I), (t, k)
     table.close()
+
+
+@pytest.mark.parametrize("d,I,r,T", [
+    (512, 1024, 5, 9), (2048, 1024, 16, 4), (2048, 1024, 64, 4), (512, 1024, 40, 30), (4096, 1024, 33, 2),
+    (8192, 1024, 32, 3), (1024, 1024, 0, 30)])
+def test_runs_per_workgroup(torch_cuda, d, I, r, T):
+    """The runs of rows a down workgroup takes at d_expert 1024: by the workgroups that
+    fit at once, up to four, and up to eight beyond rank 32."""
+    test_rows_against_oracle(torch_cuda, d, I, r, T)
