@@ -197,9 +197,23 @@ __global__ void __launch_bounds__(64 * kRouteWaves) route_mfma_kernel(const __ha
   }
 }
 
-// One wave per token: 2.5 - 3.3 us a call up to T = 777 and 4.6 us at T = 3100
-// (E 256, K 8); one 512-thread workgroup per token took 8.8 us there. For E 1000,
-// 6.7 us; a wave finding the K-th key bit by bit took 17 us.
+// One 512-thread workgroup per token (E <= 256, K <= 32): two-stage ranking of the keys
+// (moe_xchg.h), a few barriers whatever K is.
+__global__ void __launch_bounds__(512) topk_block_kernel(const float* __restrict__ logits, int E, int K,
+                                                         int32_t* __restrict__ idx, float* __restrict__ w) {
+  __shared__ float lg[256];
+  __shared__ uint64_t keys[256];
+  __shared__ int part[256];
+  __shared__ uint64_t cand[128];
+  __shared__ uint64_t sorted[32];
+  const int t = blockIdx.x;
+  if ((int)threadIdx.x < E) lg[threadIdx.x] = logits[(size_t)t * E + threadIdx.x];
+  __syncthreads();
+  eng::block_topk(lg, E, K, idx + (size_t)t * K, w + (size_t)t * K, keys, part, cand, sorted);
+}
+
+// One wave per token, K rounds: 3.6 us at T = 2048, K 8 and 6.2 us for a workgroup per
+// token. For E 1000, K 8, T = 1, 6.8 us; a wave finding the K-th key bit by bit took 17.
 template <int V>
 __global__ void __launch_bounds__(256) topk_wave_kernel(const float* __restrict__ logits, int T, int E, int K,
                                                         int32_t* __restrict__ idx, float* __restrict__ w) {
@@ -918,8 +932,18 @@ hipError_t launch_topk_sigmoid_group(const float* logits, const float* bias, int
   return hipGetLastError();
 }
 
+// A wave's time grows with K, a workgroup's with T once they fill the chip. A call,
+// workgroup / wave (us): K 8: T = 1 2.7 / 2.9, T = 256 3.1 / 3.3, T = 384 3.3 / 3.3; K 16:
+// T = 1 3.1 / 4.0, T = 640 4.1 / 4.4, T = 777 4.4 / 4.4; K 32: T = 1 3.6 / 6.0, T = 1024
+// 5.9 / 6.6, T = 1536 7.8 / 7.3; K 6: T = 1 2.7 / 2.7; K 4: 2.6 / 2.5.
+constexpr int kBlockTopkMinK = 7, kBlockTopkTokens = 40;
+
 hipError_t launch_topk(const float* logits, int T, int E, int K, int32_t* idx, float* w,
                        hipStream_t st) {
+  if (E <= 256 && K >= kBlockTopkMinK && T <= kBlockTopkTokens * K) {
+    hipLaunchKernelGGL(topk_block_kernel, dim3(T), dim3(512), 0, st, logits, E, K, idx, w);
+    return hipGetLastError();
+  }
   const dim3 grid((T + 3) / 4), block(T == 1 ? 64 : 256);
   if (E <= 256)
     hipLaunchKernelGGL(topk_wave_kernel<4>, grid, block, 0, st, logits, T, E, K, idx, w);

@@ -83,3 +83,25 @@ def test_topk_ties_and_special_values(torch_cuda, E, K):
         assert idx[t].tolist() == order.tolist(), t
         ex = np.exp(ref[t][order].astype(np.float64) - ref[t][order[0]])
         np.testing.assert_allclose(w[t], ex / ex.sum(), rtol=2e-6)
+
+
+@pytest.mark.parametrize("E,K,T", [(7, 7, 1), (7, 7, 280), (7, 7, 281), (16, 6, 1), (60, 32, 1280), (60, 32, 1281),
+                                   (255, 8, 320), (256, 8, 321), (256, 32, 64), (257, 8, 3)])
+def test_topk_by_wave_or_workgroup(torch_cuda, E, K, T):
+    """Both selections around the rule that chooses between them, on random logits and
+    on heavy ties (the lower id first)."""
+    from paper_2609_18063_amd import binding as B
+    torch = torch_cuda
+    g = np.random.default_rng(E + K + T)
+    lg = g.standard_normal((T, E)).astype(np.float32)
+    lg[T // 2] = np.round(lg[T // 2])
+    spec = B.make_spec(512, E, K, 0, 256, 0, 0.0)
+    idx = torch.full((T, K), -1, dtype=torch.int32, device="cuda")
+    w = torch.full((T, K), float("nan"), device="cuda")
+    B.topk(spec, torch.from_numpy(lg).cuda(), idx, w)
+    torch.cuda.synchronize()
+    order = np.argsort(-lg, axis=1, kind="stable")[:, :K]
+    assert np.array_equal(idx.cpu().numpy(), order)
+    top = np.take_along_axis(lg, order, 1).astype(np.float64)
+    ex = np.exp(top - top[:, :1])
+    np.testing.assert_allclose(w.cpu().numpy(), ex / ex.sum(1, keepdims=True), rtol=2e-6)
