@@ -21,16 +21,6 @@ __device__ __forceinline__ U4 ld16(const void* p) {
   return *reinterpret_cast<const U4*>(p);
 }
 
-// Cross-workgroup data (written by one workgroup and read by another in the
-// same launch) goes through agent-scope atomics so that it is coherent
-// across the XCDs' L2 caches.
-__device__ __forceinline__ void st_agent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_agent(const float* p) {
-  return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // DPP lane moves (gfx9 data-parallel primitives): a few cycles each, against
 // an LDS round trip for a shuffle.  Controls used: quad_perm [1,0,3,2] (0xB1)
 // and [2,3,0,1] (0x4E), row_half_mirror (0x141), row_mirror (0x140),

@@ -45,7 +45,6 @@ namespace pipe {
 
 using eng::claim_place;
 using eng::dma16;
-using eng::dma4;
 using eng::dma_wait;
 using eng::f64_to_h;
 using eng::kSpinMax;
@@ -185,9 +184,7 @@ struct PShape {
   static constexpr int O_DP = O_AV + NSEGX * 2 * R * 4;        // [NLX][RR] fp32 weighted down rows per expert
   static constexpr int O_YL = O_DP + NLX * RR * 4;             // [NLX][R] fp32 A_down h per expert
   static constexpr int O_LG = O_YL + NLX * R * 4;              // [256] fp32 logits
-  static constexpr int O_TK = O_LG + 256 * 4;                  // top-k scratch
-  static constexpr int TK_BYTES = 256 * 8 + 256 * 4 + 128 * 8 + 32 * 8;
-  static constexpr int O_GR = O_TK + TK_BYTES;                 // [NWV][NGW][64] fp32 gate/up lane partials
+  static constexpr int O_GR = O_LG + 256 * 4;                  // [NWV][NGW][64] fp32 gate/up lane partials
   static constexpr int O_RED = O_GR + (LPR == 64 ? NWV * NGW * 64 * 4 : 0);  // [NWV] f64
   static constexpr int O_MISC = (O_RED + NWV * 8 + 1023) / 1024 * 1024;
   static constexpr int MISC_BYTES = 5 * 1024;
@@ -239,8 +236,14 @@ struct Src {
   const uint8_t* ad[SH::NAP];       // A_down rank rows of the workgroup's (expert, rank) pairs
 };
 
-// LDS offset of the sigmoid-group selection scratch: after the whole layout
-// (16-byte aligned)
+// Scratch of the sigmoid-group selection (SIG instantiations), with that of the
+// block-wide ranking it uses
+struct SigScratch {
+  eng::SigmoidScratch sg;
+  uint64_t keys[256], cand[128], sorted[32];
+  int part[256];
+};
+// its LDS offset: after the whole layout (16-byte aligned)
 template <class SH>
 __host__ __device__ constexpr int sig_scratch_off() {
   return (SH::O_SRC + (int)sizeof(Src<SH>) + 15) / 16 * 16;
@@ -317,13 +320,7 @@ __global__ void __launch_bounds__(NT) pipe_kernel(EngineArgs) {
   float* dp = reinterpret_cast<float*>(smem + SH::O_DP);
   float* yl = reinterpret_cast<float*>(smem + SH::O_YL);
   float* lg = reinterpret_cast<float*>(smem + SH::O_LG);
-  uint64_t* tk_keys = reinterpret_cast<uint64_t*>(smem + SH::O_TK);
-  int* tk_part = reinterpret_cast<int*>(smem + SH::O_TK + 256 * 8);
-  uint64_t* tk_cand = reinterpret_cast<uint64_t*>(smem + SH::O_TK + 256 * 12);
-  uint64_t* tk_sorted = tk_cand + 128;
-  // (sigmoid-group scratch past the end of the softmax layout, in the SIG
-  // instantiation only)
-  eng::SigmoidScratch& tk_sig = *reinterpret_cast<eng::SigmoidScratch*>(smem + sig_scratch_off<SH>());
+  SigScratch& tk = *reinterpret_cast<SigScratch*>(smem + sig_scratch_off<SH>());  // (SIG only)
   using HL = HmLayout<SH>;
   char* const hmb = smem + sig_scratch_off<SH>();  // (HM instantiations only; never with SIG)
   __half* const hw1 = reinterpret_cast<__half*>(hmb + HL::O_W1);
@@ -364,7 +361,7 @@ __global__ void __launch_bounds__(NT) pipe_kernel(EngineArgs) {
   auto select = [&](const float* l, int32_t* idx_out, float* w_out) {
     if constexpr (SIG)
       eng::block_topk_sigmoid_group(l, nullptr, E, K, apx->n_groups, apx->top_groups, apx->route_scale, idx_out, w_out,
-                                    tk_sig, tk_keys, tk_part, tk_cand, tk_sorted);
+                                    tk.sg, tk.keys, tk.part, tk.cand, tk.sorted);
     else if (wave == 0)
       wave_topk<(SH::EX + 63) / 64>(l, E, K, idx_out, w_out);
   };
@@ -1288,7 +1285,7 @@ using PShape8b = PShape<4096, 1024, 16, 4, 64, 1>;
 template <class SH, bool SIG, bool HM>
 static int lds_bytes() {
   if (HM) return sig_scratch_off<SH>() + HmLayout<SH>::BYTES;
-  return SIG ? sig_scratch_off<SH>() + (int)sizeof(eng::SigmoidScratch) : SH::O_SRC + (int)sizeof(Src<SH>);
+  return SIG ? sig_scratch_off<SH>() + (int)sizeof(SigScratch) : SH::O_SRC + (int)sizeof(Src<SH>);
 }
 
 template <class SH, bool SIG, bool HM>

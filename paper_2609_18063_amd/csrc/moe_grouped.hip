@@ -12,7 +12,7 @@
 //   gate/up   per tile x 64 or 128 columns: G = X W_g^T, U = X W_u^T over the
 //             tile's rows with v_mfma_f32_16x16x32_f16; int4 codes and the
 //             activation rows stream into LDS through global_load_lds in
-//             128-k chunks of whole row segments (a ring of two to six
+//             128-k chunks of whole row segments (a ring of two to four
 //             chunks, by the tile's row count), the (s, z) rows once per
 //             tile; codes are dequantized to fp16 in registers (w = s q + z,
 //             one rounding); the LoRA delta is one MFMA step with K = the
@@ -61,6 +61,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr int kGK = 128;                        // k per staged chunk
 constexpr int kGT = 512;                        // threads of a GEMM workgroup (8 waves)
 constexpr int kGW = kGT / 64;
+constexpr int kSlots = 4;                       // slots of the chunk ring, at most
 constexpr int kCodeRow = kGK / 2;               // code bytes of one weight row in a chunk
 constexpr int kActRow = kGK * 2;                // activation bytes of one row in a chunk
 // A GEMM workgroup has eight waves; each takes NBW blocks of 16 weight rows
@@ -117,9 +118,6 @@ __device__ __forceinline__ U4 perm8(U4 w) {
   o.w = (w.y >> 16) | (w.w & 0xffff0000u);
   return o;
 }
-// position of element e (of 8) in pair order
-__device__ __forceinline__ int pair_slot(int e) { return e < 4 ? 2 * e : 2 * (e - 4) + 1; }
-
 // Eight int4 codes of one dword (nibble m = input m) -> fp16 weights
 // s q + z in pair order. A nibble masked into the mantissa of the fp16 1024
 // (0x6400) gives 1024 + q from bits 0-3 and 1024 + 16 q from bits 4-7, so
@@ -166,9 +164,9 @@ __device__ __forceinline__ h8 lora_b_operand(const __half* b, int row, int r, in
 }
 
 // ---- copies into LDS --------------------------------------------------------
-// global_load_lds: each lane of the wave moves 16 (or 4) bytes from its own
-// address to lds + 16 * lane (4 * lane). The compiler does not see these as
-// memory instructions; vm_wait orders them.
+// global_load_lds: each lane of the wave moves 16 bytes from its own address to
+// lds + 16 * lane. The compiler does not see these as memory instructions; vm_wait
+// orders them.
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
 }
@@ -184,29 +182,17 @@ __device__ __forceinline__ void dma16(const void* g, const void* lds) {
       : "s"(lds_addr(lds)), "v"(g)
       : "memory");
 }
-__device__ __forceinline__ void dma4(const void* g, const void* lds) {
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dword %2, off nt\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_addr(lds)), "v"(g)
-      : "memory");
-}
 // wait until at most N of this wave's copies are outstanding (N an immediate)
 template <int N>
 __device__ __forceinline__ void vm_wait_n() {
   static_assert(N >= 0 && N <= 63, "vmcnt range");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// the same for N = A * (hi ? PH : PL) with A = ahead in [0, 6): a short chain of
+// the same for N = A * (hi ? PH : PL) with A = ahead in [0, kSlots): a short chain of
 // scalar compares on uniform values instead of one case per count
 template <int PH, int PL, int A = 0>
 __device__ __forceinline__ void vm_wait_ahead(int ahead, bool hi) {
-  if constexpr (A < 6) {
+  if constexpr (A < kSlots) {
     if (ahead == A) {
       if (hi)
         vm_wait_n<A * PH>();
@@ -253,8 +239,8 @@ __device__ __forceinline__ void tile_gemm_mb(char* ring, char* szl, int Kdim, WR
   constexpr int NBW = V::NBW, NROWS = Shape<V>::NROWS, CR = kCodeRow, AR = kActRow;
   constexpr int CODE_B = NROWS * CR;                           // codes of a slot
   constexpr int SLOT = CODE_B + MB * 16 * AR;
-  constexpr int NBUF = V::RING / SLOT < 6 ? V::RING / SLOT : 6;
-  static_assert(NBUF >= 2, "two slots at least");
+  constexpr int NBUF = V::RING / SLOT;
+  static_assert(NBUF >= 2 && NBUF <= kSlots, "two slots at least");
   constexpr int CODE_I = NBW;                                  // code copies per wave per chunk
   constexpr int XI = MB * 16 * AR / 1024;                      // activation copies per chunk
   constexpr int JN = kGK / 32;                                 // MFMA steps of a chunk
@@ -787,8 +773,7 @@ __global__ void __launch_bounds__(kGT, V::EU) grouped_gateup_kernel(GroupedArgs 
 #pragma unroll
   for (int q = 0; q < NAX; ++q) {
     const int p = tid + q * kGT, pc = p / (TR * 16), row = (p >> 4) % TR, k = p & 15;
-    float v = axv[q][0];
-    v = (axv[q][0] + axv[q][1]) + (axv[q][2] + axv[q][3]);
+    const float v = (axv[q][0] + axv[q][1]) + (axv[q][2] + axv[q][3]);
     la[pc][row][k] = (_Float16)(a.lora_scale * v);
   }
   __syncthreads();
