@@ -48,10 +48,11 @@ WsLayout ws_layout(const moe_layer_spec* s, int T) {
   w.logits = take((size_t)T * s->n_experts * sizeof(float));
   w.gx = take((size_t)T * n * s->d_expert * sizeof(float));
   w.ux = take((size_t)T * n * s->d_expert * sizeof(float));
-  w.h = take((size_t)T * n * s->d_expert * sizeof(float));
+  const size_t h_rows = s->d_expert > moe::kHdownMaxI ? (size_t)T * n : 0;  // (else h stays in LDS)
+  w.h = take(h_rows * s->d_expert * sizeof(float));
   w.ag = take((size_t)T * n * r * sizeof(float));
   w.au = take((size_t)T * n * r * sizeof(float));
-  w.adpart = take((size_t)T * n * (s->d_expert / 64) * r * sizeof(float));
+  w.adpart = take(h_rows * (s->d_expert / 64) * r * sizeof(float));
   w.g_plan = moe::grouped_plan(T, s->d_model, s->d_expert, s->n_experts, s->top_k, s->n_shared);
   w.g_max_tiles = moe::grouped_max_tiles(T, (int)n, s->n_experts + s->n_shared, w.g_plan.tile_rows);
   // The wide plan has half as many tile records and up to twice the padding in its token

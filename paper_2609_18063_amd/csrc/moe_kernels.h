@@ -5,6 +5,8 @@
 
 namespace moe {
 
+constexpr int kHdownMaxI = 1024;  // d_expert up to which h is formed in the down launch
+
 // Everything the expert kernels need for one layer call.
 struct FfnArgs {
   int d, I, E, K, S, r, n_list;   // n_list = K + S experts per token
@@ -17,10 +19,10 @@ struct FfnArgs {
   // workspace
   float* gx;                      // [T][n][I]
   float* ux;                      // [T][n][I]
-  float* h;                       // [T][n][I]
+  float* h;                       // [T][n][I], where I > kHdownMaxI
   float* ag;                      // [T][n][r]
   float* au;                      // [T][n][r]
-  float* adpart;                  // [T][n][I/64][r]
+  float* adpart;                  // [T][n][I/64][r], where I > kHdownMaxI
   float* y_experts;               // [T][n][d]
 };
 

@@ -1014,6 +1014,7 @@ static bool dispatch_gateup(const FfnArgs& a, int T, hipStream_t st, hipEvent_t 
 }
 
 static bool dispatch_hdown(const FfnArgs& a, int T, hipStream_t st) {
+  static_assert(kHdownMaxI == 1024, "the workspace's rule is this dispatch");
   switch (a.I) {
     case 256: hdown<8, 1>(a, T, st); return true;
     case 512: hdown<16, 1>(a, T, st); return true;

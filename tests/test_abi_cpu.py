@@ -294,3 +294,21 @@ def test_current_stream_without_the_raw_reader(monkeypatch, raw):
         now[0] = value
         assert binding._stream() == value
     assert binding._stream(types.SimpleNamespace(cuda_stream=0x30)) == 0x30
+
+
+def test_workspace_holds_h_only_where_a_launch_writes_it(B):
+    """Up to d_expert 1024 the per-token call keeps h and the partials of A_down h in
+    LDS, so the workspace has no room for them there (4 + 4 r / 64 bytes a unit of
+    d_expert), and the no-allocation call takes more tokens."""
+    def per_token(I, r):
+        spec = B.make_spec(2048, 64, 4, 0, I, r, 2.0)
+        return (B.workspace_bytes(spec, 2048) - B.workspace_bytes(spec, 1024)) / 1024
+
+    for r in (8, 16):
+        # from one to two times d_expert every array of it doubles; across 1024, h
+        # (4 bytes) and the partials (4 r / 64) of the larger come in
+        base = per_token(1024, r) - per_token(512, r)
+        grown = per_token(2048, r) - per_token(1024, r)
+        assert abs(grown - 2 * base - 4 * 2048 * (4 + 4 * r / 64)) < 64 * 4, (r, base, grown)
+    spec = B.spec_from_workload(synth.WORKLOADS["moe35b"])
+    assert B.workspace_bytes(spec, 64) <= B.MOE_NOALLOC_SCRATCH_BYTES
