@@ -161,6 +161,10 @@ size_t moe_workspace_bytes(const moe_layer_spec* spec, int T);
  * logits in descending order (ties go to the lower expert id), with weights
  * w_i = exp(l_i - l_max) / sum over the selected j of exp(l_j - l_max).
  * x_f16: device fp16 [T][d]; w_router_f16: device fp16 [E][d].
+ * The order in which a logit's products are summed depends on T (row by row for few
+ * tokens, in matrix-core blocks of several sizes for many): the same token may get
+ * logits that differ in their last bits in calls of different T, and where two logits
+ * tie to that rounding, the other expert.
  * logits_opt: device fp32 [T][E], or NULL if not needed.
  * idx: device int32 [T][K]; w: device fp32 [T][K].
  */
@@ -258,7 +262,10 @@ int moe_expert_ffn_int4_lora_noalloc(const moe_layer_spec* spec, const moe_slot_
  * weights are dequantized to fp16 (w = s q + z, rounded once), the token
  * activations are fp16, h = silu(g) u is rounded to fp16 between the two
  * contractions, and lora_scale * (A v) is rounded to fp16 for the LoRA-B
- * step; every sum accumulates in fp32.
+ * step; every sum accumulates in fp32. A token's outputs do not depend on the other
+ * tokens of the call, but on how many there are: T decides over how many columns of h
+ * a partial sum of A_down h runs, so the same token may differ in the last bits
+ * between calls of different T.
  * Shapes: d and I multiples of 128, lora_rank <= 16, E + S <= 2048; other
  * specs give MOE_EINVAL. Uses the workspace of moe_workspace_bytes(spec, T).
  */
