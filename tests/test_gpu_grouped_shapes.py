@@ -139,3 +139,45 @@ def test_down_shapes(torch_cuda, counts, d, I, r, S, bad):
     """d_expert 1024 takes 128 or 256 output columns by the number of workgroups, with
     more slab partials of A_d h than are fetched before the k loop."""
     test_group_sizes(torch_cuda, counts, d, I, r, S, bad)
+
+
+@pytest.mark.parametrize("d,I,E,K,S,r,T", [(2048, 512, 16, 8, 1, 16, 1037), (4096, 1024, 16, 4, 0, 16, 1026),
+                                           (4096, 512, 12, 8, 2, 7, 900)])
+def test_wide_shape_of_long_rows(torch_cuda, d, I, E, K, S, r, T):
+    """The wide gate/up shape with 16 and 32 chunks a row, up to 64 KB of (s, z) rows and
+    several experts a token: every row against the per-token call, some against the
+    oracle."""
+    from paper_2609_18063_amd import binding as B, weights as W
+    torch = torch_cuda
+    assert T * K >= 64 * E and T * (K + S) // 128 * (I // 128) >= 256   # the wide plan's rule
+    g = np.random.default_rng(d + I + T)
+    bundles = [_bundle(g, d, I, r) for _ in range(E + S)]
+    buf, offs, _ = W.pack_host(bundles)
+    dev = W.upload(buf)
+    spec = B.make_spec(d, E, K, S, I, r, 2.0)
+    table = B.SlotTable(1, E + S, E + S)
+    W.bind_layer(table, 0, dev, offs, np.arange(E + S)[::-1])
+    table.sync()
+    x = g.standard_normal((T, d)).astype(np.float16)
+    # expert 0 in every token (the largest group), the rest at random
+    idx = np.stack([np.concatenate([[0], 1 + g.permutation(E - 1)[:K - 1]]) for _ in range(T)]).astype(np.int32)
+    xd, idxd = torch.from_numpy(x).cuda(), torch.from_numpy(idx).cuda()
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ye = torch.full((T, K + S, d), float("nan"), device="cuda")
+    ws = torch.full((B.workspace_bytes(spec, T),), 255, dtype=torch.uint8, device="cuda")
+    B.expert_ffn_grouped(spec, table, 0, xd, idxd, ye, status, ws)
+    rows = torch.full((T, K + S, d), float("nan"), device="cuda")
+    for a in range(0, T, 512):
+        n = min(512, T - a)
+        B.expert_ffn(spec, table, 0, xd[a:a + n], idxd[a:a + n], rows[a:a + n], status, ws)
+    torch.cuda.synchronize()
+    assert status.item() == 0
+    size = rows.abs().amax(-1)
+    # (the bound of test_group_sizes)
+    diff = (ye - rows).abs().amax(-1) / torch.maximum(size, size.median())
+    assert float(diff.max()) <= TOL_REL_INF
+    for t in (0, T // 2, T - 1):
+        for k, e in enumerate(list(idx[t]) + list(range(E, E + S))):
+            ref, _ = o_expert.expert_forward(bundles[e], x[t], 2.0)
+            assert rel_inf(ye[t, k].cpu().numpy(), ref) <= TOL_REL_INF, (t, k)
+    table.close()
