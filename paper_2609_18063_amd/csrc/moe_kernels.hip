@@ -51,9 +51,9 @@ __device__ __forceinline__ double block_sum_f64(double v, double* red) {
 
 // d a multiple of 4, d <= 4 NV blockDim.x
 template <int NV>
-__global__ void __launch_bounds__(1024) rmsnorm_f16_kernel(const float* __restrict__ xi, int d,
+__global__ void __launch_bounds__(512) rmsnorm_f16_kernel(const float* __restrict__ xi, int d,
                                                            __half* __restrict__ x) {
-  __shared__ double red[16];
+  __shared__ double red[8];
   const float4* row = reinterpret_cast<const float4*>(xi + (size_t)blockIdx.x * d);
   uint2* out = reinterpret_cast<uint2*>(x + (size_t)blockIdx.x * d);
   const int nv = d >> 2;
@@ -887,9 +887,11 @@ hipError_t launch_rmsnorm(const float* xi, int T, int d, __half* x, hipStream_t 
     hipLaunchKernelGGL(rmsnorm_f16_any_kernel, dim3(T), dim3(256), 0, st, xi, d, x);
     return hipGetLastError();
   }
-  // one 16-byte piece per thread while the rows are few (latency: 2.1 us at T = 1,
-  // d 2048), four waves a row once they fill the chip several times over
-  const int most = T <= 512 ? 1024 : 256;
+  // One or a few 16-byte pieces per thread while the rows are few, four waves a row once
+  // they fill the chip several times over. 256 / 512 / 1024 threads at most (us): d 2048
+  // T = 1 2.7 / 2.6, T = 512 3.3 / 3.2, T = 700 3.5 / 3.8; d 4096 T = 1 3.0 / 2.6 / 2.8,
+  // T = 512 4.1 / 4.0 / 4.6, T = 700 4.5 / 4.7 / 5.8; d 8192 T = 512 5.8 / 5.3 / 5.9.
+  const int most = T <= 512 ? 512 : 256;
   const int pieces = d / 4, threads = std::min(most, (pieces + 63) / 64 * 64);
   const int nv = (pieces + threads - 1) / threads;
   if (nv <= 1)
@@ -1049,6 +1051,8 @@ hipError_t launch_ffn(const FfnArgs& a, int T, hipStream_t st, hipEvent_t prof_s
 
 hipError_t launch_combine(const float* ye, const float* w, int T, int K, int S, int d, float* y,
                           int accumulate, hipStream_t st) {
+  // 64 / 128 / 256 threads (us): d 2048, K + S 9: T = 16 2.5 / 2.5 / 2.6, T = 512 7.7 / 6.8 /
+  // 6.6; d 512, K 2, T = 3100 5.3 / 4.3 / 4.3; d 2048, K + S 5, T = 777 - / 7.2 / 6.6.
   const int threads = T >= 64 ? 256 : 64;        // (d is a multiple of 512)
   hipLaunchKernelGGL(combine_kernel, dim3((d / 4 + threads - 1) / threads, T), dim3(threads), 0, st, ye, w, K, S, d,
                      y, accumulate);
