@@ -360,7 +360,7 @@ __global__ void __launch_bounds__(NT) pipe_kernel(EngineArgs) {
   // sigmoid-group selection where the spec asks for it. (One wave's rounds: with the
   // block's ranking and its barriers, both in turn on one box, five times: 4 tokens of
   // 40 layers 2,233-2,242 us against 2,229-2,234, 4 launches of 24 layers of the 8B-tier
-  // shape 1,892-1,906 against 1,884-1,889, a single call of either the other way.)
+  // shape 1,892-1,906 against 1,884-1,889.)
   auto select = [&](const float* l, int32_t* idx_out, float* w_out) {
     if constexpr (SIG)
       eng::block_topk_sigmoid_group(l, nullptr, E, K, apx->n_groups, apx->top_groups, apx->route_scale, idx_out, w_out,
