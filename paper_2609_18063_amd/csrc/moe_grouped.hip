@@ -29,16 +29,18 @@
 // permutation; the operands of the epilogue (LoRA rows, A x, the output rows)
 // are requested before the copies and consumed after the k loop.
 //
-// Per launch at d 2048, I 512, E 256, K 8, S 1, before / now (us): T = 64 permute
-// 6.7 / 7.6, prep 12.0 / 9.1, gate/up 49 / 41, down 32 / 26; T = 512 10.8 / 9.4,
-// 19.9 / 15.4, 95 / 80, 62 / 51; T = 3100 39 / 25, 51 / 43, 274 / 214, 197 / 152. At
-// d 4096, I 1024, E 64, K 4: T = 37 gate/up 64 / 44 (two workgroups a CU at 48 KB of
-// ring, one at 56), T = 777 174 / 122, down 83 / 70. A gate/up workgroup of one row
+// Per launch at d 2048, I 512, E 256, K 8, S 1, with one workgroup permuting, narrow
+// shapes only and tiles in group order / now (us, means of 20 traced calls): T = 64
+// permute 6.7 / 5.3, prep 12.0 / 9.4, gate/up 49 / 42, down 32 / 26; T = 512 10.8 / 7.7,
+// 19.9 / 14.9, 95 / 83, 62 / 51; T = 3100 39 / 24, 51 / 42, 274 / 221, 197 / 153. At
+// d 4096, I 1024, E 64, K 4: T = 37 gate/up 64 / 45 (two workgroups a CU at 48 KB of
+// ring, one at 56), T = 777 174 / 130, down 83 / 72. A gate/up workgroup of one row
 // block is bound by the dequantization (13 VALU instructions per 8 codes, 0.54 us a
 // chunk for the two of a CU) and by its start: 6 of its 16 us pass before its first
 // chunk is there. One of eight row blocks spends 2.3 us a chunk on 1.0 us of matrix
-// instructions and 0.5 us of VALU: without its copies the launch takes 175 us of 200,
-// without the matrix instructions 160, without the dequantization 176.
+// instructions and 0.5 us of VALU: a probe build's T = 3100 launch of 200 us took 175
+// without its copies, 160 without the matrix instructions, 176 without the
+// dequantization.
 //
 // Pair order: inside each 8-element piece the elements run [0,4,1,5,2,6,3,7],
 // the order in which the packed nibbles of one code dword come out of a
