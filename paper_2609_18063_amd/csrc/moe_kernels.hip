@@ -937,8 +937,8 @@ hipError_t launch_topk_sigmoid_group(const float* logits, const float* bias, int
 // A wave's time grows with K, a workgroup's with T once they fill the chip. A call,
 // workgroup / wave (us): K 8: T = 1 2.7 / 2.9, T = 256 3.1 / 3.3, T = 384 3.3 / 3.3; K 16:
 // T = 1 3.1 / 4.0, T = 640 4.1 / 4.4, T = 777 4.4 / 4.4; K 32: T = 1 3.6 / 6.0, T = 1024
-// 5.9 / 6.6, T = 1536 7.8 / 7.3; K 6: T = 1 2.7 / 2.7; K 4: 2.6 / 2.5.
-constexpr int kBlockTopkMinK = 7, kBlockTopkTokens = 40;
+// 5.9 / 6.6, T = 1536 7.8 / 7.3; K 6: T = 64 3.0 / 3.1, T = 256 3.1 / 3.1; K 4: T = 1 2.6 / 2.5.
+constexpr int kBlockTopkMinK = 6, kBlockTopkTokens = 40;
 
 hipError_t launch_topk(const float* logits, int T, int E, int K, int32_t* idx, float* w,
                        hipStream_t st) {
@@ -986,6 +986,9 @@ static void down(const FfnArgs& a, int T, hipStream_t st) {
 // rank 32, whose h costs most. K + S 5, one run / this rule / h in a launch of its own:
 // d 4096, T = 1, r 5 29.9 / 25.2 / 26.7 us, r 64 77 / 41.6 / 65; d 2048, T = 2, r 16
 // 25.0 / 22.0 / 30.3; d 512, T = 8, r 64 80.5 / 41.8 / 56.
+// Rank 0, whose h costs least, takes half the runs where long workgroups would be a round
+// and a rest below a half: K + S 9, d 4096, T = 8 116.3 / 109.4 / 116.3; K + S 5, d 2048,
+// T = 64 231 / 214 / 241.
 constexpr int kHdownFill = 512;
 template <int LPR, int CPL>
 static void hdown(const FfnArgs& a, int T, hipStream_t st) {
@@ -997,6 +1000,7 @@ static void hdown(const FfnArgs& a, int T, hipStream_t st) {
   if (32 * LPR * CPL > 512) {
     const int resident = a.r > 32 ? 256 : 512, most = a.r > 32 ? 8 : 4;
     while (2 * batches <= std::min(runs, most) && all / batches > resident) batches *= 2;
+    if (a.r == 0 && batches >= 8 && all / batches > 512 && all / batches < 768) batches /= 2;
   }
   hipLaunchKernelGGL((ffn_hdown_kernel<LPR, CPL, RIT>), dim3(runs / batches * a.n_list, T), dim3(256), 0, st, a,
                      batches);

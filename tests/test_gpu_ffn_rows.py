@@ -72,8 +72,9 @@ def test_rows_against_oracle(torch_cuda, d, I, r, T):
 
 @pytest.mark.parametrize("d,I,r,T", [
     (512, 1024, 5, 9), (2048, 1024, 16, 4), (2048, 1024, 64, 4), (512, 1024, 40, 30), (4096, 1024, 33, 2),
-    (8192, 1024, 32, 3), (1024, 1024, 0, 30)])
+    (8192, 1024, 32, 3), (1024, 1024, 0, 30), (4096, 1024, 0, 24)])
 def test_runs_per_workgroup(torch_cuda, d, I, r, T):
     """The runs of rows a down workgroup takes at d_expert 1024: by the workgroups that
-    fit at once, up to four, and up to eight beyond rank 32."""
+    fit at once, up to four, up to eight beyond rank 32, and half as many at rank 0 where
+    the last round would be short."""
     test_rows_against_oracle(torch_cuda, d, I, r, T)

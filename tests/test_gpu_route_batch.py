@@ -85,7 +85,7 @@ def test_topk_ties_and_special_values(torch_cuda, E, K):
         np.testing.assert_allclose(w[t], ex / ex.sum(), rtol=2e-6)
 
 
-@pytest.mark.parametrize("E,K,T", [(7, 7, 1), (7, 7, 280), (7, 7, 281), (16, 6, 1), (60, 32, 1280), (60, 32, 1281),
+@pytest.mark.parametrize("E,K,T", [(7, 7, 1), (7, 7, 280), (7, 7, 281), (16, 5, 1), (16, 6, 1), (16, 6, 240), (16, 6, 241), (60, 32, 1280), (60, 32, 1281),
                                    (255, 8, 320), (256, 8, 321), (256, 32, 64), (257, 8, 3)])
 def test_topk_by_wave_or_workgroup(torch_cuda, E, K, T):
     """Both selections around the rule that chooses between them, on random logits and
